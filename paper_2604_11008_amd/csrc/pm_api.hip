@@ -1216,40 +1216,51 @@ pm_status pm_autotune(pm_ctx *ctx, const pm_field *field, const pm_decomp *decom
     return PM_OK;
 }
 
-// Layout of the re-sort workspace.
-struct SortLayout {
-    size_t keys[2], vals[2], hist, off, total;
-    int64_t tiles;
-};
-
-static SortLayout sort_layout(int64_t pool_extent, int32_t nsub)
+// Bytes of the re-sort workspace: per record two 8-byte keys and two 4-byte
+// positions, and per 8192 records and per segment 256 counts and positions.
+static size_t sort_bytes(int64_t pool_extent, int32_t nsub)
 {
-    SortLayout L{};
+    const size_t pe = (size_t)std::max<int64_t>(pool_extent, 1);
+    const size_t tiles = (size_t)(pool_extent / 8192) + (size_t)nsub + 1;
+    return 2 * align256(pe * sizeof(uint64_t)) + 2 * align256(pe * sizeof(uint32_t)) +
+           align256(tiles * 256 * sizeof(uint32_t)) + align256(tiles * 256 * sizeof(int64_t));
+}
+
+// The arrays of a re-sort in its workspace w: the pairs, then the tile places,
+// counts and totals.  32-bit keys take half the keys' room, which leaves the
+// rest for 9-bit digits; false where `bits` does not fit.
+static bool bind_sort(pm::DSort &d, char *w, int64_t pool_extent, int32_t nsub, bool wide,
+                      int bits)
+{
     const size_t pe = (size_t)std::max<int64_t>(pool_extent, 1);
     const size_t tiles = (size_t)(pool_extent / pm::sort_tile()) + (size_t)nsub + 1;
-    L.tiles = (int64_t)tiles;
+    const size_t ks = wide ? sizeof(uint64_t) : sizeof(uint32_t);
     size_t o = 0;
     for (int b = 0; b < 2; ++b) {
-        L.keys[b] = o;
-        o += align256(pe * sizeof(uint64_t));
+        d.keys[b] = w + o;
+        o += align256(pe * ks);
     }
     for (int b = 0; b < 2; ++b) {
-        L.vals[b] = o;
+        d.vals[b] = (uint32_t *)(w + o);
         o += align256(pe * sizeof(uint32_t));
     }
-    L.hist = o;
-    o += align256(tiles * 256 * sizeof(uint32_t));
-    L.off = o;
-    o += align256(tiles * 256 * sizeof(int64_t));
-    L.total = o;
-    return L;
+    d.place = (pm::SortTile *)(w + o);
+    o += align256(tiles * sizeof(pm::SortTile));
+    d.hist = (uint32_t *)(w + o);
+    o += align256((tiles << bits) * sizeof(uint32_t));
+    d.tot = (uint32_t *)(w + o);
+    o += align256(((size_t)nsub << bits) * sizeof(uint32_t));
+    d.tiles = (int64_t)tiles;
+    d.wide = wide;
+    d.bits = bits;
+    return o <= sort_bytes(pool_extent, nsub);
 }
 
 size_t pm_sort_workspace_bytes(int64_t pool_extent, int32_t nsub)
 {
     if (pool_extent < 0 || pool_extent >= ((int64_t)1 << 32) || nsub < 1 || nsub > PM_MAX_NSUB)
         return 0;
-    return sort_layout(pool_extent, nsub).total;
+    return sort_bytes(pool_extent, nsub);
 }
 
 pm_status pm_sort(pm_ctx *ctx, const pm_field *field, const pm_particles *in,
@@ -1275,37 +1286,39 @@ pm_status pm_sort(pm_ctx *ctx, const pm_field *field, const pm_particles *in,
         return arg_error("in and out must be different pools");
     if (ctx->ws.pool_extent >= ((int64_t)1 << 32))
         return arg_error("the re-sort takes pool extents below 2^32");
-    const SortLayout L = sort_layout(ctx->ws.pool_extent, in->nsub);
-    if (!workspace || ws_bytes < L.total)
+    const int64_t pe = ctx->ws.pool_extent;
+    const size_t need = sort_bytes(pe, in->nsub);
+    if (!workspace || ws_bytes < need)
         return arg_error("sort workspace of %zu bytes is smaller than the %zu needed", ws_bytes,
-                         L.total);
+                         need);
     if (((uintptr_t)workspace & 255u) != 0)
         return arg_error("sort workspace must be 256-byte aligned");
-    char *w = (char *)workspace;
-    pm::DSort d;
-    for (int b = 0; b < 2; ++b) {
-        d.keys[b] = (uint64_t *)(w + L.keys[b]);
-        d.vals[b] = (uint32_t *)(w + L.vals[b]);
-    }
-    d.hist = (uint32_t *)(w + L.hist);
-    d.off = (int64_t *)(w + L.off);
-    d.tiles = L.tiles;
-    // radix passes over the key's bits: 3 bits per Z-order level plus the
-    // parity bit of x
+    // the key's bits: 3 per Z-order level plus the parity bit of x
     int m = std::max({(field->n[0] - 1) >> 1, field->n[1] - 1, field->n[2] - 1, 1});
     int bits = 0;
     while (m) {
         ++bits;
         m >>= 1;
     }
-    const int passes = (3 * bits + 1 + 7) / 8;
+    const int key_bits = 3 * bits + 1;
+    // 64-bit keys only for grids beyond 1024 cells an axis.  9-bit digits where
+    // they save a pass (256^3: three instead of four) and their tables fit.
+    const bool wide = key_bits > 32;
+    pm::DSort d;
+    const bool nine = !wide && (key_bits + 8) / 9 < (key_bits + 7) / 8 &&
+                      bind_sort(d, (char *)workspace, pe, in->nsub, false, 9);
+    if (!nine && !bind_sort(d, (char *)workspace, pe, in->nsub, wide, 8))
+        return arg_error("sort workspace layout");
+    const int passes = (key_bits + d.bits - 1) / d.bits;
     k.sub_first = 0;
     k.sub_count = in->nsub;
     k.tile = pm::sort_tile();
     hipStream_t st = (hipStream_t)stream;
     PM_HIP(pm::launch_prep(k, pm::kPrepTiles | pm::kPrepCheckIn | pm::kPrepCheckOut, st),
            "prep launch");
-    PM_HIP(pm::launch_sort(k, d, passes, mixed, std::max(1, ctx->cus * 4), st), "sort launch");
+    // at most: the tiles are counted on the device
+    const int64_t tiles = pe / pm::sort_tile() + in->nsub;
+    PM_HIP(pm::launch_sort(k, d, passes, mixed, tiles, ctx->cus, st), "sort launch");
     return PM_OK;
 }
 

@@ -110,15 +110,25 @@ struct KArgs {
     int32_t cpt;         // append: workgroups per destination
 };
 
+// A tile of the cell re-sort: first record, records, segment, and the segment
+// counted from the range's first.
+struct SortTile {
+    uint32_t first;
+    int32_t nitems, seg, sl;
+};
+
 // Work arrays of the cell re-sort (a caller-owned workspace of its own):
 // (key, pool position) pairs in two buffers ping-ponged by the radix passes,
-// and per tile the digit counts and the pool positions they start at.
+// per tile the digit counts, which the scan replaces by the records of equal
+// digit in earlier tiles, and per segment the digit totals.
 struct DSort {
-    uint64_t *keys[2];   // [pool_extent]
+    void *keys[2];       // [pool_extent] uint32_t, or uint64_t if wide
     uint32_t *vals[2];   // [pool_extent]
-    uint32_t *hist;      // [tiles * 256]
-    int64_t *off;        // [tiles * 256]
-    int64_t tiles;       // capacity of hist and off, in tiles
+    SortTile *place;     // [tiles]
+    uint32_t *hist;      // [tiles << bits]
+    uint32_t *tot;       // [nsub << bits]
+    int64_t tiles;       // capacity of place and hist, in tiles
+    int32_t wide, bits;  // 64-bit keys; bits of a digit
 };
 
 // Prep kernel modes.
@@ -140,10 +150,10 @@ struct Shape {
 // Launchers (pm_kernels.hip).  `mixed` selects float32 field/velocities.
 hipError_t launch_prep(const KArgs &a, int mode, hipStream_t st);
 // Cell re-sort (pm_sort.hip): records per tile, and the launches of one sort
-// (keys, `passes` radix passes of 8 bits, gather).
+// (keys, `passes` radix passes of s.bits bits, gather) over at most `tiles` tiles.
 int sort_tile();
-hipError_t launch_sort(const KArgs &a, DSort s, int passes, bool mixed, int grid,
-                       hipStream_t st);
+hipError_t launch_sort(const KArgs &a, const DSort &s, int passes, bool mixed, int64_t tiles,
+                       int cus, hipStream_t st);
 hipError_t launch_step(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st);
 hipError_t launch_advance(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st);
 hipError_t launch_classify(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st);

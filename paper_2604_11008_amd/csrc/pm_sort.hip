@@ -6,8 +6,14 @@
 // tens of steps.  Order within each segment: by the cell key (Z-order over
 // pairs of cells along x, then the parity of the cell's x index), ties by
 // input position -- a stable least-significant-digit radix sort of
-// (key, position) pairs, 8 bits per pass, over tiles that never straddle a
-// segment, followed by one gather of the records.  Every scatter and gather
+// (key, position) pairs over tiles that never straddle a segment, followed by
+// one gather of the records.  Keys are 32 bits up to 1024 cells an axis; a
+// pass takes 9 bits where that saves a pass (25-bit keys of 256^3: three
+// instead of four), else 8.  One sort of 4.2 million records in 64 segments of
+// 256^3 cells, 25 steps after the last: 0.31 ms against 0.61 ms with 64-bit
+// keys and tiles of 8192 records in rounds of 256 (keys 35 us, three passes of
+// counts 6, scan 5 and scatter 27, gather 143; the records alone, read and
+// written once, are 107 us at the 5 TB/s of a plain copy).  Every scatter and gather
 // index is checked against its segment's range; a violation sets PM_F_LAYOUT
 // instead of writing.
 #include "pm_device.h"
@@ -15,14 +21,26 @@
 namespace pm {
 namespace {
 
-constexpr int kSortWG = 256;
-constexpr int kSortItems = 32;
+constexpr int kSortWG = 512;
+constexpr int kSortItems = 8;
 constexpr int kSortTile = kSortWG * kSortItems;
+constexpr int kSortWaves = kSortWG / 64;
 constexpr int kScanBatch = 32;  // tiles whose counts a scan thread loads at once
+constexpr int kScanParts = 8;   // threads that share a digit's tiles in the scan
 
-// The 21 low bits of v moved to bits 0, 3, 6, ..., 60 (the magic-mask bit
-// spreading of Morton encoding: five shift-or-mask steps).
-__device__ __forceinline__ uint64_t spread3(uint32_t v)
+// The 10 (21) low bits of v moved to bits 0, 3, 6, ... (the magic-mask bit
+// spreading of Morton encoding: shift-or-mask steps).
+__device__ __forceinline__ uint32_t spread3(uint32_t v, uint32_t)
+{
+    uint32_t x = v & 0x3ffu;
+    x = (x | x << 16) & 0x30000ffu;
+    x = (x | x << 8) & 0x300f00fu;
+    x = (x | x << 4) & 0x30c30c3u;
+    x = (x | x << 2) & 0x9249249u;
+    return x;
+}
+
+__device__ __forceinline__ uint64_t spread3(uint32_t v, uint64_t)
 {
     uint64_t x = v & 0x1fffffu;
     x = (x | x << 32) & 0x1f00000000ffffull;
@@ -35,10 +53,11 @@ __device__ __forceinline__ uint64_t spread3(uint32_t v)
 
 // Z-order code of (i >> 1, j, k) (bit b of each at 3b, 3b+1, 3b+2), times
 // two, plus the parity of i.
-__device__ __forceinline__ uint64_t cell_key(int i, int j, int k)
+template <typename KT>
+__device__ __forceinline__ KT cell_key(int i, int j, int k)
 {
-    const uint64_t code = spread3((uint32_t)i >> 1) | spread3((uint32_t)j) << 1 |
-                          spread3((uint32_t)k) << 2;
+    const KT code = spread3((uint32_t)i >> 1, KT()) | spread3((uint32_t)j, KT()) << 1 |
+                    spread3((uint32_t)k, KT()) << 2;
     return code * 2 + ((uint32_t)i & 1u);
 }
 
@@ -70,234 +89,372 @@ __device__ __forceinline__ int64_t sort_tiles(const KArgs &a, const DSort &s)
     return total;
 }
 
-// Keys and positions of every record of the range, at the record's own pool
-// position.
-__global__ __launch_bounds__(kSortWG) void k_sort_keys(const KArgs a, DSort s)
+// One record of each active lane into the digit counts.  The high digits of a
+// segment's keys, and the keys of a dense cell, are often the same in a whole
+// wave: one addition then, instead of one after the other to one address.
+__device__ __forceinline__ void count_digit(uint32_t *cnt, uint32_t d)
 {
-    const int64_t total = sort_tiles(a, s);
-    if (total < 0)
-        return;
-    for (int64_t q = blockIdx.x; q < total; q += gridDim.x) {
-        TileHead h;
-        locate(a, kSortTile, q, h, a.ws.tile_start);
-        for (int i = threadIdx.x; i < h.nitems; i += kSortWG) {
-            const int64_t p = h.first + i;
-            const int ci = cell_of(a.in.x[0][p], a.f.r[0], a.f.n[0]);
-            const int cj = cell_of(a.in.x[1][p], a.f.r[1], a.f.n[1]);
-            const int ck = cell_of(a.in.x[2][p], a.f.r[2], a.f.n[2]);
-            s.keys[0][p] = cell_key(ci, cj, ck);
-            s.vals[0][p] = (uint32_t)p;
-        }
-    }
+    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+    const uint64_t active = __ballot(true);
+    if (__ballot(d == d0) != active)
+        atomicAdd(&cnt[d], 1u);
+    else if ((int)__lane_id() == __ffsll((unsigned long long)active) - 1)
+        atomicAdd(&cnt[d], (uint32_t)__popcll(active));
 }
 
-// Per tile: the counts of the pass's digit.
-__global__ __launch_bounds__(kSortWG) void k_sort_hist(const KArgs a, DSort s, int src,
-                                                        int shift)
+// Keys and positions of every record of the range, at the record's own pool
+// position; per tile its place in the pool (the later kernels read it instead
+// of searching the tile table again) and the counts of the first digit.
+template <typename KT, int ND>
+__global__ __launch_bounds__(kSortWG) void k_sort_keys(const KArgs a, DSort s)
 {
-    __shared__ uint32_t cnt[256];
+    __shared__ uint32_t cnt[ND];
+    __shared__ TileHead H;
     const int64_t total = sort_tiles(a, s);
     if (total < 0)
         return;
     const int tid = threadIdx.x;
+    KT *keys = (KT *)s.keys[0];
     for (int64_t q = blockIdx.x; q < total; q += gridDim.x) {
-        TileHead h;
-        locate(a, kSortTile, q, h, a.ws.tile_start);
-        cnt[tid] = 0;
-        __syncthreads();
-        for (int i = tid; i < h.nitems; i += kSortWG) {
-            const uint32_t d = (uint32_t)(s.keys[src][h.first + i] >> shift) & 255u;
-            atomicAdd(&cnt[d], 1u);
+        for (int d = tid; d < ND; d += kSortWG)
+            cnt[d] = 0;
+        if (tid == 0) {
+            locate(a, kSortTile, q, H, a.ws.tile_start);
+            s.place[q] = SortTile{(uint32_t)H.first, H.nitems, H.s, H.sl};
         }
         __syncthreads();
-        s.hist[q * 256 + tid] = cnt[tid];
+        const int64_t first = H.first;
+        const int nitems = H.nitems;
+        for (int i = tid; i < nitems; i += kSortWG) {
+            const int64_t p = first + i;
+            const int ci = cell_of(a.in.x[0][p], a.f.r[0], a.f.n[0]);
+            const int cj = cell_of(a.in.x[1][p], a.f.r[1], a.f.n[1]);
+            const int ck = cell_of(a.in.x[2][p], a.f.r[2], a.f.n[2]);
+            const KT key = cell_key<KT>(ci, cj, ck);
+            keys[p] = key;
+            s.vals[0][p] = (uint32_t)p;
+            count_digit(cnt, (uint32_t)key & (ND - 1));
+        }
+        __syncthreads();
+        for (int d = tid; d < ND; d += kSortWG)
+            s.hist[q * ND + d] = cnt[d];
         __syncthreads();
     }
 }
 
-// Per segment (one workgroup of 1024 threads: digit d = tid mod 256, part =
-// tid / 256 takes a quarter of the segment's tiles): the pool position where
-// each tile's records of digit d go -- the segment's base, plus the records
-// of smaller digits in the segment, plus those of digit d in earlier tiles.
-constexpr int kScanParts = 4;
-
-__global__ __launch_bounds__(256 * kScanParts) void k_sort_scan(const KArgs a, DSort s)
+// Per tile: the counts of the pass's digit.
+template <typename KT, int ND>
+__global__ __launch_bounds__(kSortWG) void k_sort_hist(const KArgs a, DSort s, int src,
+                                                        int shift)
 {
-    __shared__ int64_t part_sum[kScanParts][256];
-    __shared__ int64_t wave_tot[4];
+    __shared__ uint32_t cnt[ND];
+    const int64_t total = sort_tiles(a, s);
+    if (total < 0)
+        return;
+    const int tid = threadIdx.x;
+    const KT *keys = (const KT *)s.keys[src];
+    for (int64_t q = blockIdx.x; q < total; q += gridDim.x) {
+        const SortTile t = s.place[q];
+        for (int d = tid; d < ND; d += kSortWG)
+            cnt[d] = 0;
+        KT key[kSortItems];
+#pragma unroll
+        for (int k = 0; k < kSortItems; ++k) {
+            const int i = k * kSortWG + tid;
+            key[k] = keys[t.first + (i < t.nitems ? i : t.nitems - 1)];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSortItems; ++k)
+            if (k * kSortWG + tid < t.nitems)
+                count_digit(cnt, (uint32_t)(key[k] >> shift) & (ND - 1));
+        __syncthreads();
+        for (int d = tid; d < ND; d += kSortWG)
+            s.hist[q * ND + d] = cnt[d];
+        __syncthreads();
+    }
+}
+
+// Per (segment, 64 digits): a tile's count of a digit becomes the records of
+// that digit in the segment's earlier tiles, in place; the segment's totals
+// beside.  Lane = digit, so every load is one run; each wave takes one of
+// kScanParts equal shares of the tiles.
+template <int ND>
+__global__ __launch_bounds__(64 * kScanParts) void k_sort_scan(const KArgs a, DSort s)
+{
+    __shared__ uint32_t part_sum[kScanParts][64];
     if (sort_tiles(a, s) < 0)
         return;
-    const int tid = threadIdx.x, d = tid & 255, part = tid >> 8;
-    for (int sl = blockIdx.x; sl < a.sub_count; sl += gridDim.x) {
+    const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+    const int64_t jobs = (int64_t)a.sub_count * (ND / 64);
+    for (int64_t job = blockIdx.x; job < jobs; job += gridDim.x) {
+        const int64_t sl = job / (ND / 64);
+        const int d = (int)(job % (ND / 64)) * 64 + lane;
         const int64_t t0 = a.ws.tile_start[sl], t1 = a.ws.tile_start[sl + 1];
         const int64_t len = (t1 - t0 + kScanParts - 1) / kScanParts;
         const int64_t p0 = t0 + part * len, p1 = p0 + len < t1 ? p0 + len : t1;
-        // this part's count of digit d
-        int64_t tot = 0;
+        uint32_t tot = 0;
         int64_t t = p0;
         for (; t + kScanBatch <= p1; t += kScanBatch) {
             uint32_t c[kScanBatch];
 #pragma unroll
             for (int u = 0; u < kScanBatch; ++u)
-                c[u] = s.hist[(t + u) * 256 + d];
+                c[u] = s.hist[(t + u) * ND + d];
 #pragma unroll
             for (int u = 0; u < kScanBatch; ++u)
                 tot += c[u];
         }
         for (; t < p1; ++t)
-            tot += s.hist[t * 256 + d];
-        part_sum[part][d] = tot;
+            tot += s.hist[t * ND + d];
+        part_sum[part][lane] = tot;
         __syncthreads();
-        // digit totals, scanned over the digits by the first 256 threads
-        int64_t digit_tot = 0;
+        uint32_t run = 0, all = 0;
 #pragma unroll
-        for (int q = 0; q < kScanParts; ++q)
-            digit_tot += part_sum[q][d];
-        int64_t incl = digit_tot;
-        const int lane = tid & 63, w = tid >> 6;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int lo = __shfl_up((int)(uint32_t)incl, off, 64);
-            const int hi = __shfl_up((int)(uint32_t)((uint64_t)incl >> 32), off, 64);
-            const int64_t v = (int64_t)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo);
-            if (lane >= off)
-                incl += v;
+        for (int q = 0; q < kScanParts; ++q) {
+            const uint32_t c = part_sum[q][lane];
+            run += q < part ? c : 0u;
+            all += c;
         }
-        if (tid < 256 && lane == 63)
-            wave_tot[w] = incl;
-        __syncthreads();
-        // every part of digit d starts after the smaller digits, then after
-        // the earlier parts of digit d
-        int64_t run = a.in.base[a.sub_first + sl] + incl - digit_tot;
-        for (int v = 0; v < (d >> 6); ++v)
-            run += wave_tot[v];
-        for (int q = 0; q < part; ++q)
-            run += part_sum[q][d];
+        if (part == 0)
+            s.tot[sl * ND + d] = all;
         t = p0;
         for (; t + kScanBatch <= p1; t += kScanBatch) {
             uint32_t c[kScanBatch];
 #pragma unroll
             for (int u = 0; u < kScanBatch; ++u)
-                c[u] = s.hist[(t + u) * 256 + d];
+                c[u] = s.hist[(t + u) * ND + d];
 #pragma unroll
             for (int u = 0; u < kScanBatch; ++u) {
-                s.off[(t + u) * 256 + d] = run;
+                s.hist[(t + u) * ND + d] = run;
                 run += c[u];
             }
         }
         for (; t < p1; ++t) {
-            const uint32_t c = s.hist[t * 256 + d];
-            s.off[t * 256 + d] = run;
+            const uint32_t c = s.hist[t * ND + d];
+            s.hist[t * ND + d] = run;
             run += c;
         }
-        __syncthreads();  // part_sum and wave_tot are reused by the next segment
+        __syncthreads();  // part_sum is reused by the next job
     }
 }
 
 // Per tile: every record to its place for this digit, in tile order among
-// the records of equal digit (so each pass is stable).  Rounds of 256
-// consecutive records: a record's rank is the number of records of its digit
-// before it in its wave (ballots over the 8 digit bits), in the earlier waves
-// of the round, and in the earlier rounds.
+// the records of equal digit (so each pass is stable).  The tile's 4096 keys
+// are read at once, each wave's 512 in order; a record's rank among its
+// wave's earlier records of the same digit comes from ballots over the digit's
+// bits and the wave's own counters in LDS (no barrier), the waves' counts and
+// the digits are scanned once, and the tile leaves through LDS in digit order,
+// so that the stores of a digit are runs.  Bound by the latency of a tile's
+// few dependent steps: 4.2 million records (256^3 cells, 64 segments) pass in
+// 26-29 us; rounds of 256 records, three barriers and a dependent load each,
+// took 42-79 us.  8 items on 512 threads rather than 16 on 256: 128 registers
+// instead of 190.
+template <typename KT, int BITS>
 __global__ __launch_bounds__(kSortWG) void k_sort_scatter(const KArgs a, DSort s, int src,
                                                            int shift)
 {
-    __shared__ int64_t run[256];
-    __shared__ uint32_t wc[4][256];
+    constexpr int ND = 1 << BITS;
+    static_assert(ND <= kSortWG, "one digit a thread");
+    __shared__ uint32_t cnt[kSortWaves][ND];
+    __shared__ uint32_t place[ND];  // pool position of a digit's run, less its start in the tile
+    __shared__ KT box[kSortTile];
+    __shared__ uint64_t wave_tot[kSortWaves];
     const int64_t total = sort_tiles(a, s);
     if (total < 0)
         return;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int dst = src ^ 1;
+    const KT *kin = (const KT *)s.keys[src];
+    KT *kout = (KT *)s.keys[dst];
     uint32_t fl = 0;
     for (int64_t q = blockIdx.x; q < total; q += gridDim.x) {
-        TileHead h;
-        locate(a, kSortTile, q, h, a.ws.tile_start);
-        const int64_t lo = a.in.base[h.s], hi = lo + a.in.count[h.s];
-        run[tid] = s.off[q * 256 + tid];
+        const SortTile t = s.place[q];
+        const uint32_t lo = (uint32_t)a.in.base[t.seg], n = (uint32_t)a.in.count[t.seg];
+        KT key[kSortItems];
+        uint32_t val[kSortItems], rank[kSortItems];
+        const int i0 = w * (64 * kSortItems) + lane;  // item k: record i0 + 64 k
+        const KT *kp = kin + t.first + i0;
+        const uint32_t *vp = s.vals[src] + t.first + i0;
+        if (t.nitems == kSortTile) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            wc[v][tid] = 0;
-        __syncthreads();
-        for (int r = 0; r < kSortItems; ++r) {
-            const int i = r * kSortWG + tid;
-            const bool valid = i < h.nitems;
-            uint64_t key = 0;
-            uint32_t val = 0, d = 0;
-            if (valid) {
-                key = s.keys[src][h.first + i];
-                val = s.vals[src][h.first + i];
-                d = (uint32_t)(key >> shift) & 255u;
+            for (int k = 0; k < kSortItems; ++k) {
+                key[k] = kp[64 * k];
+                val[k] = vp[64 * k];
             }
+        } else {
+#pragma unroll
+            for (int k = 0; k < kSortItems; ++k) {
+                key[k] = 0;
+                val[k] = 0;
+                if (i0 + 64 * k < t.nitems) {
+                    key[k] = kp[64 * k];
+                    val[k] = vp[64 * k];
+                }
+            }
+        }
+        uint32_t off = 0, seg_tot = 0;  // of digit tid
+        if (tid < ND) {
+            off = s.hist[q * ND + tid];
+            seg_tot = s.tot[(int64_t)t.sl * ND + tid];
+#pragma unroll
+            for (int v = 0; v < kSortWaves; ++v)
+                cnt[v][tid] = 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSortItems; ++k) {
+            const bool valid = i0 + 64 * k < t.nitems;
+            const uint32_t d = (uint32_t)(key[k] >> shift) & (ND - 1);
             uint64_t m = __ballot(valid);
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
+            for (int b = 0; b < BITS; ++b) {
                 const bool bit = (d >> b) & 1u;
-                const uint64_t bb = __ballot(valid && bit);
+                const uint64_t bb = __ballot(bit);
                 m &= bit ? bb : ~bb;
             }
-            const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
-            const uint32_t rank = (uint32_t)__popcll(m & below);
-            if (valid && lane == 63 - __clzll(m))
-                wc[w][d] = (uint32_t)__popcll(m);
-            __syncthreads();
-            if (valid) {
-                int64_t o = run[d] + rank;
-                for (int v = 0; v < w; ++v)
-                    o += wc[v][d];
-                if (o >= lo && o < hi) {
-                    s.keys[dst][o] = key;
-                    s.vals[dst][o] = val;
+            const uint64_t below = m & ((1ull << lane) - 1ull);
+            // one wave's LDS operations run in order; the barriers only keep
+            // the compiler from moving them across each other
+            __builtin_amdgcn_wave_barrier();
+            const uint32_t before = cnt[w][d];
+            __builtin_amdgcn_wave_barrier();
+            if (valid && below == 0)
+                cnt[w][d] = before + (uint32_t)__popcll(m);
+            rank[k] = before + (uint32_t)__popcll(below);
+            __builtin_amdgcn_sched_barrier(0);  // or all 16 masks are kept at once
+        }
+        __syncthreads();
+        // starts of the digits in the tile and (high half) in the segment
+        uint32_t wc[kSortWaves], mine = 0;
+        if (tid < ND) {
+#pragma unroll
+            for (int v = 0; v < kSortWaves; ++v) {
+                wc[v] = mine;
+                mine += cnt[v][tid];
+            }
+        }
+        const uint64_t sum = (uint64_t)seg_tot << 32 | mine;
+        uint64_t incl = sum;
+#pragma unroll
+        for (int sh = 1; sh < 64; sh <<= 1) {
+            const uint32_t l = (uint32_t)__shfl_up((int)(uint32_t)incl, sh, 64);
+            const uint32_t h = (uint32_t)__shfl_up((int)(uint32_t)(incl >> 32), sh, 64);
+            if (lane >= sh)
+                incl += (uint64_t)h << 32 | l;
+        }
+        if (lane == 63)
+            wave_tot[w] = incl;
+        __syncthreads();
+        uint64_t run = incl - sum;
+#pragma unroll
+        for (int v = 0; v < kSortWaves; ++v)
+            run += v < w ? wave_tot[v] : 0;
+        if (tid < ND) {
+            const uint32_t start = (uint32_t)run;
+            place[tid] = lo + (uint32_t)(run >> 32) + off - start;
+#pragma unroll
+            for (int v = 0; v < kSortWaves; ++v)
+                cnt[v][tid] = start + wc[v];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSortItems; ++k) {
+            rank[k] += cnt[w][(uint32_t)(key[k] >> shift) & (ND - 1)];
+            if (i0 + 64 * k < t.nitems)
+                box[rank[k]] = key[k];
+        }
+        __syncthreads();
+        uint32_t to[kSortItems];
+#pragma unroll
+        for (int k = 0; k < kSortItems; ++k) {
+            const int i = k * kSortWG + tid;
+            if (i < t.nitems) {
+                const KT kk = box[i];
+                to[k] = place[(uint32_t)(kk >> shift) & (ND - 1)] + i;
+                if (to[k] - lo < n) {
+                    kout[to[k]] = kk;
                 } else {
+                    to[k] = ~0u;
                     fl |= PM_F_LAYOUT;
                 }
             }
-            __syncthreads();
-            run[tid] += wc[0][tid] + wc[1][tid] + wc[2][tid] + wc[3][tid];
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                wc[v][tid] = 0;
-            __syncthreads();
         }
+        __syncthreads();
+        uint32_t *vbox = (uint32_t *)box;
+#pragma unroll
+        for (int k = 0; k < kSortItems; ++k)
+            if (i0 + 64 * k < t.nitems)
+                vbox[rank[k]] = val[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < kSortItems; ++k) {
+            const int i = k * kSortWG + tid;
+            if (i < t.nitems && to[k] != ~0u)
+                s.vals[dst][to[k]] = vbox[i];
+        }
+        __syncthreads();
     }
     if (fl)
         flag_or(a.ws.hdr, fl);
 }
 
 // The records in sorted order: out[out.base[s] + r] = in[vals[in.base[s] + r]].
+// A workgroup takes half a tile, four records a thread, whose loads (8 arrays
+// each) are all in flight at once: 143 us on 4.2 million records, against 203
+// with a tile of 8192 a workgroup, one record after the other.
 template <typename FT>
 __global__ __launch_bounds__(kSortWG) void k_sort_gather(const KArgs a, DSort s, int src)
 {
+    constexpr int U = 4, Q = kSortItems / U;
     const int64_t total = sort_tiles(a, s);
     if (total < 0)
         return;
     uint32_t fl = 0;
-    for (int64_t q = blockIdx.x; q < total; q += gridDim.x) {
-        TileHead h;
-        locate(a, kSortTile, q, h, a.ws.tile_start);
-        const int64_t lo = a.in.base[h.s], hi = lo + a.in.count[h.s];
-        const int64_t obase = a.out.base[h.s], ocap = a.out.cap[h.s];
-        for (int i = threadIdx.x; i < h.nitems; i += kSortWG) {
-            const int64_t p = h.first + i;
-            const int64_t from = (int64_t)s.vals[src][p];
-            const int64_t r = p - lo;
-            if (from < lo || from >= hi) {
+    for (int64_t job = blockIdx.x; job < total * Q; job += gridDim.x) {
+        const SortTile t = s.place[job / Q];
+        const uint32_t lo = (uint32_t)a.in.base[t.seg], n = (uint32_t)a.in.count[t.seg];
+        const int64_t obase = a.out.base[t.seg], ocap = a.out.cap[t.seg];
+        uint32_t from[U];
+        int64_t to[U];
+        bool ok[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = (int)(job % Q) * (U * kSortWG) + u * kSortWG + threadIdx.x;
+            ok[u] = i < t.nitems;
+            const uint32_t p = t.first + (ok[u] ? i : 0);
+            from[u] = s.vals[src][p];
+            to[u] = p - lo;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (ok[u] && from[u] - lo >= n) {
                 fl |= PM_F_LAYOUT;
-                continue;
+                ok[u] = false;
             }
-            if (r >= ocap) {
+            if (ok[u] && to[u] >= ocap) {
                 fl |= PM_F_DEST_OVERFLOW;
-                continue;
+                ok[u] = false;
             }
-            const int64_t to = obase + r;
+            from[u] = ok[u] ? from[u] : lo;  // a record of the segment: never written
+            to[u] += obase;
+        }
+        double x[U][3];
+        FT v[U][3], tau[U];
+        uint64_t id[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                a.out.x[c][to] = a.in.x[c][from];
-                ((FT *)a.out.v[c])[to] = ((const FT *)a.in.v[c])[from];
+                x[u][c] = a.in.x[c][from[u]];
+                v[u][c] = ((const FT *)a.in.v[c])[from[u]];
             }
-            ((FT *)a.out.tau)[to] = ((const FT *)a.in.tau)[from];
-            a.out.id[to] = a.in.id[from];
+            tau[u] = ((const FT *)a.in.tau)[from[u]];
+            id[u] = a.in.id[from[u]];
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (ok[u])
+                put_record<FT>(a.out, to[u], x[u], v[u], tau[u], id[u]);
     }
     for (int64_t sl = (int64_t)blockIdx.x * kSortWG + threadIdx.x; sl < a.sub_count;
          sl += (int64_t)gridDim.x * kSortWG) {
@@ -310,23 +467,53 @@ __global__ __launch_bounds__(kSortWG) void k_sort_gather(const KArgs a, DSort s,
         flag_or(a.ws.hdr, fl);
 }
 
+// The workgroups of a launch over `work` jobs: one each up to eight a compute
+// unit (512 threads each, all the chip holds), the rest in strides.
+int sort_grid(int64_t work, int cus)
+{
+    return (int)std::max<int64_t>(1, std::min<int64_t>(work, (int64_t)cus * 8));
+}
+
+template <typename KT, int BITS>
+hipError_t sort_passes(const KArgs &a, const DSort &s, int passes, int64_t tiles, int cus,
+                       hipStream_t st, int *last)
+{
+    const int grid = sort_grid(tiles, cus);
+    hipLaunchKernelGGL((k_sort_keys<KT, 1 << BITS>), dim3(grid), dim3(kSortWG), 0, st, a, s);
+    int src = 0;
+    for (int p = 0; p < passes; ++p) {
+        if (p)
+            hipLaunchKernelGGL((k_sort_hist<KT, 1 << BITS>), dim3(grid), dim3(kSortWG), 0, st,
+                               a, s, src, BITS * p);
+        hipLaunchKernelGGL((k_sort_scan<1 << BITS>),
+                           dim3(sort_grid((int64_t)a.sub_count << (BITS - 6), cus)),
+                           dim3(64 * kScanParts), 0, st, a, s);
+        hipLaunchKernelGGL((k_sort_scatter<KT, BITS>), dim3(grid), dim3(kSortWG), 0, st, a, s,
+                           src, BITS * p);
+        src ^= 1;
+    }
+    *last = src;
+    return hipGetLastError();
+}
+
 }  // namespace
 
 int sort_tile() { return kSortTile; }
 
-hipError_t launch_sort(const KArgs &a, DSort s, int passes, bool mixed, int grid,
-                       hipStream_t st)
+hipError_t launch_sort(const KArgs &a, const DSort &s, int passes, bool mixed, int64_t tiles,
+                       int cus, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_sort_keys, dim3(grid), dim3(kSortWG), 0, st, a, s);
     int src = 0;
-    for (int p = 0; p < passes; ++p) {
-        hipLaunchKernelGGL(k_sort_hist, dim3(grid), dim3(kSortWG), 0, st, a, s, src, 8 * p);
-        hipLaunchKernelGGL(k_sort_scan, dim3(std::max(1, std::min(a.sub_count, 4096))),
-                           dim3(256 * kScanParts), 0, st, a, s);
-        hipLaunchKernelGGL(k_sort_scatter, dim3(grid), dim3(kSortWG), 0, st, a, s, src,
-                           8 * p);
-        src ^= 1;
-    }
+    hipError_t e;
+    if (s.wide)
+        e = sort_passes<uint64_t, 8>(a, s, passes, tiles, cus, st, &src);
+    else if (s.bits == 9)
+        e = sort_passes<uint32_t, 9>(a, s, passes, tiles, cus, st, &src);
+    else
+        e = sort_passes<uint32_t, 8>(a, s, passes, tiles, cus, st, &src);
+    if (e != hipSuccess)
+        return e;
+    const int grid = sort_grid(tiles * 2, cus);
     if (mixed)
         hipLaunchKernelGGL(k_sort_gather<float>, dim3(grid), dim3(kSortWG), 0, st, a, s, src);
     else

@@ -694,17 +694,19 @@ pm_status pm_classify_scan_pack(pm_ctx *ctx, const pm_decomp *decomp, const pm_p
     hipStream_t st = (hipStream_t)stream;
     k.sub_first = sub_first;
     k.sub_count = sub_count;
-    const pm::Shape sh = shape_for(ctx, mixed, false);
-    k.tile = sh.wg * sh.items;
+    // tiles of the scan: 4096 records where the pool gives every compute unit
+    // two of them (the look-back passes over fewer tiles), else 1024 or 256
+    const int64_t pe = ctx->ws.pool_extent, cus = ctx->cus;
+    const int items = pe >= 4096 * 2 * cus ? 16 : (pe >= 1024 * 2 * cus ? 4 : 1);
+    (void)shape_for(ctx, mixed, false);  // the shape pm_get_tuning reports
+    k.tile = 256 * items;
+    k.xg = k.xb = 1;
     PM_HIP(pm::launch_prep(k,
                            pm::kPrepTiles | pm::kPrepStaging | pm::kPrepZeroLb |
                                pm::kPrepZeroCounts | pm::kPrepCheckIn | pm::kPrepCheckSend,
                            st),
            "prep launch");
-    const int grid = persistent_grid(ctx, sh, mixed, false, false, pm::kFieldSplit);
-    set_groups(ctx, k, grid);
-    PM_HIP(pm::launch_classify(k, sh, mixed, grid, st),
-           "classify launch");
+    PM_HIP(pm::launch_classify(k, mixed, items, ctx->cus, st), "classify launch");
     PM_HIP(pm::launch_route(k, mixed, false, st), "route launch");
     return PM_OK;
 }
@@ -739,15 +741,15 @@ pm_status pm_compact_append(pm_ctx *ctx, const pm_decomp *decomp, const pm_parti
     hipStream_t st = (hipStream_t)stream;
     k.sub_first = sub_first;
     k.sub_count = sub_count;
-    const pm::Shape sh = shape_for(ctx, mixed, false);
-    k.tile = sh.wg * sh.items;
+    const int items = ctx->ws.pool_extent >= 1024 * 2 * (int64_t)ctx->cus ? 4 : 1;
+    (void)shape_for(ctx, mixed, false);
+    k.tile = 256 * items;
     k.cpt = append_cpt(sub_count);
     PM_HIP(pm::launch_prep(k, pm::kPrepTiles | pm::kPrepCheckIn | pm::kPrepCheckOut |
                                   pm::kPrepCheckSend,
                            st),
            "prep launch");
-    const int cgrid = persistent_grid(ctx, sh, mixed, false, false, pm::kFieldSplit);
-    PM_HIP(pm::launch_compact(k, sh, mixed, cgrid, st), "compact launch");
+    PM_HIP(pm::launch_compact(k, mixed, items, ctx->cus, st), "compact launch");
     const int grid = std::min(4096, sub_count * k.cpt);
     PM_HIP(pm::launch_append(k, mixed, std::max(1, grid), st), "append launch");
     return PM_OK;

@@ -15,7 +15,6 @@ constexpr uint64_t kLbA = 1ull << 62;     // tile aggregate published
 constexpr uint64_t kLbP = 2ull << 62;     // inclusive prefix published
 constexpr uint64_t kLbMask = (1ull << 62) - 1;
 constexpr uint64_t kM31 = 0x7fffffffull;
-constexpr uint32_t kMigrantSlot = 0xffffffffu;
 
 // Smallest tile any launch shape uses; sizes the look-back workspace.
 constexpr int kMinTile = 256;
@@ -78,7 +77,8 @@ struct DWS {
     int64_t *migtot;       // [nsub] leavers per segment
     int64_t *stg_start;    // [PM_MAX_NSUB + 1] staging offset of each segment of the range
     uint64_t *lb;          // [max_tiles] look-back status words
-    uint32_t *slot;        // [pool_extent] stayer slots (plain path)
+    uint32_t *slot;        // [pool_extent] stayers before each run of 64 records of a
+                           // segment, at the run's first record (plain path)
     // staging of the leavers, in scan order per segment: [stg_extent]
     double *stg_x[3];
     double *stg_v[3];      // read as float in the mixed mode
@@ -156,8 +156,8 @@ hipError_t launch_sort(const KArgs &a, const DSort &s, int passes, bool mixed, i
                        int cus, hipStream_t st);
 hipError_t launch_step(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st);
 hipError_t launch_advance(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st);
-hipError_t launch_classify(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st);
-hipError_t launch_compact(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st);
+hipError_t launch_classify(const KArgs &a, bool mixed, int items, int cus, hipStream_t st);
+hipError_t launch_compact(const KArgs &a, bool mixed, int items, int cus, hipStream_t st);
 hipError_t launch_append(const KArgs &a, bool mixed, int grid, hipStream_t st);
 hipError_t launch_route(const KArgs &a, bool mixed, bool append, hipStream_t st,
                         bool ext = false);

@@ -112,7 +112,10 @@ void bind_ws(pm::DWS &ws, char *w, const WsLayout &L, int64_t pool_extent,
     ws.stay = (int64_t *)(w + L.stay);
     ws.migtot = (int64_t *)(w + L.migtot);
     ws.stg_start = (int64_t *)(w + L.stg_start);
-    ws.lb = (uint64_t *)(w + L.lb);
+    // 8 bytes a tile: 2 of status (read in words of 4 tiles), and behind them
+    // the 4 bytes per 64 tiles and per segment that are handed on
+    ws.status = (uint16_t *)(w + L.lb);
+    ws.handed = (uint32_t *)(w + L.lb + (size_t)((L.max_tiles + 3) >> 2) * sizeof(uint64_t));
     ws.slot = slot ? (uint32_t *)(w + L.slot) : nullptr;
     const size_t fs = align256((size_t)L.stg_extent * 8);
     char *g = w + L.stg;

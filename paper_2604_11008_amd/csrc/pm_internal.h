@@ -9,11 +9,7 @@
 
 namespace pm {
 
-// Look-back status word of a tile: the tile's count of stayers (bits 0-30)
-// and of leavers (bits 31-61), and a 2-bit state (bits 62-63).
-constexpr uint64_t kLbA = 1ull << 62;     // tile aggregate published
-constexpr uint64_t kLbP = 2ull << 62;     // inclusive prefix published
-constexpr uint64_t kLbMask = (1ull << 62) - 1;
+// Most records of a segment.
 constexpr uint64_t kM31 = 0x7fffffffull;
 
 // Smallest tile any launch shape uses; sizes the look-back workspace.
@@ -76,7 +72,9 @@ struct DWS {
     int64_t *stay;         // [nsub] stayers per segment
     int64_t *migtot;       // [nsub] leavers per segment
     int64_t *stg_start;    // [PM_MAX_NSUB + 1] staging offset of each segment of the range
-    uint64_t *lb;          // [max_tiles] look-back status words
+    uint16_t *status;      // [max_tiles] look-back: a tile's leavers + 1, 0 until known
+    uint32_t *handed;      // [max_tiles / 64 + nsub + 1] leavers of a segment up to the end
+                           // of each 64 of its tiles, + 1
     uint32_t *slot;        // [pool_extent] stayers before each run of 64 records of a
                            // segment, at the run's first record (plain path)
     // staging of the leavers, in scan order per segment: [stg_extent]

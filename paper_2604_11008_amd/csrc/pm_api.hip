@@ -206,6 +206,7 @@ pm_status conv_field(const pm_field *f, pm::DField &d, bool &mixed)
     d.stagger = f->stagger;
     d.layout = f->layout;
     d.sx = sx;
+    d.sy = sy;
     d.sxy = sx * sy;
     mixed = f->dtype == PM_F32;
     return PM_OK;

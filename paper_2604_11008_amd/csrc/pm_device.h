@@ -100,9 +100,19 @@ __device__ __forceinline__ void owner_xyz(const DDecomp &dc, int s, int own[3])
 // trilinear interpolation (Sect. 2.2)
 // ---------------------------------------------------------------------------
 
+// (int)x of an integral double, saturating; 0 for a NaN.
+__device__ __forceinline__ int to_int(double x)
+{
+    int i;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(i) : "v"(x));
+    return i;
+}
+
 // Stored corner indices of one axis and the cell fraction (float64); half is
 // the nodes' offset in cells: 1/2 for cell centres, 0 for the faces of a
-// MAC component along its own axis.
+// MAC component along its own axis.  A position whose stencil leaves the
+// stored grid (periodic: more than a box away) raises PM_F_HALO and is moved
+// to the nearest stored corner.  No branches: six of these run per record.
 template <bool HALO>
 __device__ __forceinline__ double axis_corner(const DField &f, int a, double X, double half,
                                               int &c0, uint32_t &fl)
@@ -110,35 +120,16 @@ __device__ __forceinline__ double axis_corner(const DField &f, int a, double X, 
     const int n = f.n[a];
     const double s = X * f.r[a] - half;
     const double fs = floor(s);
-    int i;
-    if (s != s) {
-        i = 0;
-    } else if (HALO) {
-        if (!(s >= -1.0)) {
-            fl |= PM_F_HALO;
-            i = -1;
-        } else if (!(s < (double)n)) {
-            fl |= PM_F_HALO;
-            i = n - 1;
-        } else {
-            i = (int)fs;
-        }
-    } else {
-        if (!(s >= -(double)n)) {
-            fl |= PM_F_HALO;
-            i = -n;
-        } else if (!(s < 2.0 * (double)n)) {
-            fl |= PM_F_HALO;
-            i = 2 * n - 1;
-        } else {
-            i = (int)fs;
-        }
-    }
-    if (HALO) {
-        c0 = i + 1;
-    } else {
-        c0 = i < 0 ? i + n : (i >= n ? i - n : i);
-    }
+    const int i = to_int(fs);  // saturated where out of range, 0 for a NaN
+    // periodic: whichever of i, i + n, i - n lies in [0, n) is the smallest
+    // as unsigned
+    const uint32_t u = HALO ? (uint32_t)i + 1u
+                            : min(min((uint32_t)i, (uint32_t)i + (uint32_t)n), (uint32_t)i - (uint32_t)n);
+    const uint32_t top = HALO ? (uint32_t)n : (uint32_t)n - 1u;
+    const bool out = u > top;
+    if (out)
+        fl |= PM_F_HALO;
+    c0 = (int)(out ? top & ~(uint32_t)(i >> 31) : u);
     return s - fs;
 }
 
@@ -189,55 +180,75 @@ __device__ __forceinline__ void load_six(const FT *p, FT w[6])
         w[i] = q.w[i];
 }
 
-// The 24 node values of a stencil: v[c][2*r + x] for component c, row r
-// (y and z corner: 00, 10, 01, 11) and x corner x.  Split arrays: each
-// row's x pair of a component is one load.  Interleaved (ILV, the three
-// components of a node next to each other): each row's two nodes are one
-// run of six values.  Where a periodic field wraps (x corner n-1, then 0)
-// the run starts one node earlier and the node at 0 is loaded on its own
-// (n >= 2).
-template <typename FT, bool HALO, bool ILV>
-__device__ __forceinline__ void stencil_load(const DField &f, const int c0[3], FT v[3][8])
+// Stored index of the lower x corner of a stencil's four rows (y and z corner:
+// 00, 10, 01, 11).
+template <bool HALO>
+__device__ __forceinline__ void stencil_rows(const DField &f, const int c0[3], int64_t r[4])
 {
-    const int cx1 = next_corner<HALO>(f, 0, c0[0]);
-    const int cy1 = next_corner<HALO>(f, 1, c0[1]);
-    const int cz1 = next_corner<HALO>(f, 2, c0[2]);
-    const int64_t r[4] = {f.sx * (int64_t)c0[1] + f.sxy * (int64_t)c0[2],
-                          f.sx * (int64_t)cy1 + f.sxy * (int64_t)c0[2],
-                          f.sx * (int64_t)c0[1] + f.sxy * (int64_t)cz1,
-                          f.sx * (int64_t)cy1 + f.sxy * (int64_t)cz1};
-    const bool wrap = !HALO && cx1 != c0[0] + 1;
-    const int xa = wrap ? c0[0] - 1 : c0[0];
-    if constexpr (ILV) {
-        const FT *u = (const FT *)f.u[0];
+    const uint64_t row = (uint64_t)(uint32_t)c0[2] * (uint32_t)f.sy + (uint32_t)c0[1];
+    r[0] = (int64_t)(row * (uint32_t)f.sx + (uint32_t)c0[0]);
+    const int64_t dy = HALO || c0[1] + 1 != f.n[1] ? f.sx : f.sx - f.sxy;
+    const int64_t dz = HALO || c0[2] + 1 != f.n[2] ? f.sxy : f.sxy - f.sxy * f.n[2];
+    r[1] = r[0] + dy;
+    r[2] = r[0] + dz;
+    r[3] = r[2] + dy;
+}
+
+// Whether a stencil of any lane of the wave wraps around a periodic field
+// along x, so that its rows are not runs of two nodes.  Rare (one cell in n),
+// and decided for the whole wave on interleaved fields: with a branch per lane
+// around the wrapped nodes' loads every wave copied the 24 values once more and
+// waited for them there (2 x 10^7 records in 512 subdomains, float64: 1.31 ms
+// so, 1.15 without; split fields run no slower with it).
+template <bool HALO>
+__device__ __forceinline__ bool any_wrap(bool wraps)
+{
+    return !HALO && __ballot(wraps) != 0;
+}
+
+// The 24 node values of a stencil: v[c][2*r + x] for component c, row r and x
+// corner x.  Interleaved (ILV, the three components of a node next to each
+// other): each row's two nodes are one run of six values; the stencil must not
+// wrap along x (any_wrap).
+template <typename FT>
+__device__ __forceinline__ void stencil_load_ilv(const DField &f, const int64_t r[4], FT v[3][8])
+{
+    const FT *u = (const FT *)f.u[0];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            FT w[6];
-            load_six<FT>(u + 3 * (r[k] + xa), w);
+    for (int k = 0; k < 4; ++k) {
+        FT w[6];
+        load_six<FT>(u + 3 * r[k], w);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                v[c][2 * k] = w[c];
-                v[c][2 * k + 1] = w[3 + c];
-            }
+        for (int c = 0; c < 3; ++c) {
+            v[c][2 * k] = w[c];
+            v[c][2 * k + 1] = w[3 + c];
         }
-        if (wrap) {
-#pragma unroll
-            for (int c = 0; c < 3; ++c)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    v[c][2 * k] = v[c][2 * k + 1];
-                    v[c][2 * k + 1] = u[3 * (r[k] + cx1) + c];
-                }
-        }
-        return;
     }
+}
+
+// Split arrays: each row's x pair of a component is one load.  Where a
+// periodic field wraps (x corner n-1, then 0) the run starts one node earlier
+// and the node at 0 is loaded on its own (n >= 2).  APART: one component after
+// the other, so that a line that two rows of a component share is asked for
+// once or found, where the compiler's own order (row by row over the
+// components) asks for it again while it is in flight.
+template <typename FT, bool HALO, bool APART>
+__device__ __forceinline__ void stencil_load_split(const DField &f, const int c0[3],
+                                                   const int64_t r[4], FT v[3][8])
+{
+    const bool wrap = !HALO && c0[0] + 1 == f.n[0];
+    const int back = wrap ? 1 : 0;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         const FT *u = (const FT *)f.u[c];
+        if (APART)
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int k = 0; k < 4; ++k)
-            load_pair<FT>(u + r[k] + xa, v[c][2 * k], v[c][2 * k + 1]);
+            load_pair<FT>(u + r[k] - back, v[c][2 * k], v[c][2 * k + 1]);
     }
+    if (APART)
+        __builtin_amdgcn_sched_barrier(0);
     if (wrap) {
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
@@ -245,10 +256,25 @@ __device__ __forceinline__ void stencil_load(const DField &f, const int c0[3], F
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 v[c][2 * k] = v[c][2 * k + 1];
-                v[c][2 * k + 1] = u[r[k] + cx1];
+                v[c][2 * k + 1] = u[r[k] + 1 - f.n[0]];
             }
         }
     }
+}
+
+// Measured, APART against the compiler's order: interpolation at 4.2 million
+// points of a split 256^3 field 0.186 ms against 0.206, the step with a halo
+// 0.330 against 0.335; the periodic step, which has a second stencil to wait
+// for anyway, 3.64 against 3.57 (2^26 records, 512^3).
+template <typename FT, bool HALO, bool ILV, bool APART = HALO>
+__device__ __forceinline__ void stencil_load(const DField &f, const int c0[3], FT v[3][8])
+{
+    int64_t r[4];
+    stencil_rows<HALO>(f, c0, r);
+    if constexpr (ILV)
+        stencil_load_ilv<FT>(f, r, v);
+    else
+        stencil_load_split<FT, HALO, APART>(f, c0, r, v);
 }
 
 // U from a loaded stencil: x-, then y-, then z-lerps.
@@ -291,24 +317,19 @@ __device__ __forceinline__ void mac_index(const DField &f, const double X[3], in
 template <typename FT, bool HALO>
 __device__ __forceinline__ void comp_load(const DField &f, int comp, const int c0[3], FT v[8])
 {
-    const int cx1 = next_corner<HALO>(f, 0, c0[0]);
-    const int cy1 = next_corner<HALO>(f, 1, c0[1]);
-    const int cz1 = next_corner<HALO>(f, 2, c0[2]);
-    const int64_t r[4] = {f.sx * (int64_t)c0[1] + f.sxy * (int64_t)c0[2],
-                          f.sx * (int64_t)cy1 + f.sxy * (int64_t)c0[2],
-                          f.sx * (int64_t)c0[1] + f.sxy * (int64_t)cz1,
-                          f.sx * (int64_t)cy1 + f.sxy * (int64_t)cz1};
+    int64_t r[4];
+    stencil_rows<HALO>(f, c0, r);
     const FT *u = (const FT *)f.u[comp];
-    const bool wrap = !HALO && cx1 != c0[0] + 1;
-    const int xa = wrap ? c0[0] - 1 : c0[0];
+    const bool wrap = !HALO && c0[0] + 1 == f.n[0];
+    const int back = wrap ? 1 : 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        load_pair<FT>(u + r[k] + xa, v[2 * k], v[2 * k + 1]);
+        load_pair<FT>(u + r[k] - back, v[2 * k], v[2 * k + 1]);
     if (wrap) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
             v[2 * k] = v[2 * k + 1];
-            v[2 * k + 1] = u[r[k] + cx1];
+            v[2 * k + 1] = u[r[k] + 1 - f.n[0]];
         }
     }
 }
@@ -319,6 +340,28 @@ __device__ __forceinline__ FT comp_eval(const FT v[8], const FT fr[3])
     const FT l00 = lerp(v[0], v[1], fr[0]), l10 = lerp(v[2], v[3], fr[0]);
     const FT l01 = lerp(v[4], v[5], fr[0]), l11 = lerp(v[6], v[7], fr[0]);
     return lerp(lerp(l00, l10, fr[1]), lerp(l01, l11, fr[1]), fr[2]);
+}
+
+// U at one stencil of a periodic interleaved field, every node loaded by
+// itself: for the waves with a stencil that wraps along x.
+template <typename FT>
+__device__ __forceinline__ void interp_wrapped(const DField &f, const int c0[3], const FT fr[3],
+                                               FT U[3])
+{
+    int64_t r[4];
+    stencil_rows<false>(f, c0, r);
+    const int64_t dx = c0[0] + 1 != f.n[0] ? 1 : 1 - (int64_t)f.n[0];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const FT *u = (const FT *)f.u[0] + c;
+        FT v[8];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[2 * k] = u[3 * r[k]];
+            v[2 * k + 1] = u[3 * (r[k] + dx)];
+        }
+        U[c] = comp_eval<FT>(v, fr);
+    }
 }
 
 // U(X) by trilinear interpolation (Sect. 2.2) from a field of arrangement FA.
@@ -341,7 +384,11 @@ __device__ __forceinline__ void interp(const DField &f, const double X[3], FT U[
     int c0[3];
     FT fr[3], v[3][8];
     stencil_index<FT, HALO>(f, X, c0, fr, fl);
-    stencil_load<FT, HALO, FA == kFieldIlv>(f, c0, v);
+    if (FA == kFieldIlv && any_wrap<HALO>(c0[0] == f.n[0] - 1)) {
+        interp_wrapped<FT>(f, c0, fr, U);
+        return;
+    }
+    stencil_load<FT, HALO, FA == kFieldIlv, true>(f, c0, v);
     stencil_eval<FT>(v, fr, U);
 }
 
@@ -377,9 +424,8 @@ __device__ __forceinline__ FT drag_factor(FT kappa, FT tau, const FT s[3])
 }
 
 // Heun step of one particle.  The stage-2 position X* = X + dt V does not
-// depend on the stage-1 interpolation, so both stencils are located first
-// and fetched in one round trip; most stage-2 stencils fall in the stage-1
-// cell and are not fetched again.  NL: the nonlinear drag factor, else f = 1.
+// depend on the stage-1 interpolation, so both stencils are located first;
+// most stage-2 stencils fall in the stage-1 cell and are not fetched again.  NL: the nonlinear drag factor, else f = 1.
 template <typename FT, bool HALO, bool NL, int FA>
 __device__ __forceinline__ void advance_one(const KArgs &a, double X[3], FT V[3], FT tau,
                                             uint32_t &fl)
@@ -390,6 +436,7 @@ __device__ __forceinline__ void advance_one(const KArgs &a, double X[3], FT V[3]
     for (int c = 0; c < 3; ++c)
         Xs[c] = fma(a.dt, (double)V[c], X[c]);
     FT U1[3], U2[3];
+    const int last = a.f.n[0] - 1;
     if constexpr (FA == kFieldMac) {
         int c1[3][3], c2[3][3];
         FT fr1[3][3], fr2[3][3], S1[3][8], S2[3][8];
@@ -411,19 +458,34 @@ __device__ __forceinline__ void advance_one(const KArgs &a, double X[3], FT V[3]
             U2[c] = moved[c] ? comp_eval<FT>(S2[c], fr2[c]) : comp_eval<FT>(S1[c], fr2[c]);
         }
     } else {
+        constexpr bool ILV = FA == kFieldIlv;
         int c1[3], c2[3];
-        FT fr1[3], fr2[3], S1[3][8], S2[3][8];
+        FT fr1[3], fr2[3];
         stencil_index<FT, HALO>(a.f, X, c1, fr1, fl);
         stencil_index<FT, HALO>(a.f, Xs, c2, fr2, fl);
-        const bool moved = c2[0] != c1[0] || c2[1] != c1[1] || c2[2] != c1[2];
-        stencil_load<FT, HALO, FA == kFieldIlv>(a.f, c1, S1);
-        if (moved)
-            stencil_load<FT, HALO, FA == kFieldIlv>(a.f, c2, S2);
-        stencil_eval<FT>(S1, fr1, U1);
-        if (moved)
-            stencil_eval<FT>(S2, fr2, U2);
-        else
-            stencil_eval<FT>(S1, fr2, U2);
+        if (ILV && any_wrap<HALO>(c1[0] == last || c2[0] == last)) {
+            interp_wrapped<FT>(a.f, c1, fr1, U1);
+            interp_wrapped<FT>(a.f, c2, fr2, U2);
+        } else {
+            const bool moved = c2[0] != c1[0] || c2[1] != c1[1] || c2[2] != c1[2];
+            FT S1[3][8], S2[3][8];
+            stencil_load<FT, HALO, ILV>(a.f, c1, S1);
+            // the second stencils lie mostly on the first ones' lines: issued
+            // once those have arrived they hit, issued along with them they ask
+            // for every line again (2^26 records on a split 512^3 field: 3.7 ms
+            // so, 3.8 with both in flight); the first stencil is evaluated while
+            // they come
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            if (moved)
+                stencil_load<FT, HALO, ILV>(a.f, c2, S2);
+            stencil_eval<FT>(S1, fr1, U1);
+            if (moved)
+                stencil_eval<FT>(S2, fr2, U2);
+            else
+                stencil_eval<FT>(S1, fr2, U2);
+        }
     }
     FT A1[3], Vs[3], s1[3], s2[3];
     const FT it = (FT)1 / tau;
@@ -1028,10 +1090,10 @@ __device__ __forceinline__ void scatter_stash(const KArgs &a, const TileLds<WG, 
                                               const TileStash<WG, ITEMS, FT> &S, uint32_t &fl)
 {
     const int tid = threadIdx.x;
-    const int s = L.h.s;
+    const int s = uniform(L.h.s), sl = uniform(L.h.sl);
     const int64_t obase = a.out.base[s], ocap = a.out.cap[s];
-    const int64_t g0 = a.ws.stg_start[L.h.sl];
-    const int64_t gcap = a.ws.stg_start[L.h.sl + 1] - g0;
+    const int64_t g0 = a.ws.stg_start[sl];
+    const int64_t gcap = a.ws.stg_start[sl + 1] - g0;
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int i = k * WG + tid;
@@ -1097,9 +1159,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(ITEMS >= 8 ?
 
     while (next_tile<WG, ITEMS>(a, L[cur], total, ts, pend)) {
         TileLds<WG, ITEMS> &C = L[cur];
-        const int s = C.h.s;
-        const int64_t first = C.h.first;
-        const int nitems = C.h.nitems;
+        const int s = uniform(C.h.s);
+        const int64_t first = uniform(C.h.first);
+        const int nitems = uniform(C.h.nitems);
         int own[3];
         owner_xyz(a.dc, s, own);
 
@@ -1132,9 +1194,11 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(ITEMS >= 8 ?
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
             d[k] = 0xff;
-            if (k * WG + tid < nitems) {
+            if (k * WG + uniform(w) * 64 < nitems) {  // a wave with any record
                 advance_one<FT, HALO, NL, FA>(a, X[k], V[k], tau[k], fl);
                 d[k] = classify(a.dc, own, X[k], fl);
+                if (k * WG + tid >= nitems)
+                    d[k] = 0xff;
             }
         }
         __builtin_amdgcn_s_setprio(0);
@@ -1860,10 +1924,10 @@ __device__ __forceinline__ void scatter_stash_x(const KArgs &a, const TileLds<WG
                                                 uint32_t &fl)
 {
     const int tid = threadIdx.x;
-    const int s = L.h.s;
+    const int s = uniform(L.h.s), sl = uniform(L.h.sl);
     const int64_t obase = a.out.base[s], ocap = a.out.cap[s];
-    const int64_t g0 = a.ws.stg_start[L.h.sl];
-    const int64_t gcap = a.ws.stg_start[L.h.sl + 1] - g0;
+    const int64_t g0 = a.ws.stg_start[sl];
+    const int64_t gcap = a.ws.stg_start[sl + 1] - g0;
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int i = k * WG + tid;
@@ -1924,9 +1988,9 @@ __global__ __launch_bounds__(WG) void k_stage(const KArgs a)
 
     while (next_tile<WG, ITEMS>(a, L[cur], total, a.ws.tile_start, pend)) {
         TileLds<WG, ITEMS> &C = L[cur];
-        const int s = C.h.s;
-        const int64_t first = C.h.first;
-        const int nitems = C.h.nitems;
+        const int s = uniform(C.h.s);
+        const int64_t first = uniform(C.h.first);
+        const int nitems = uniform(C.h.nitems);
         int own[3];
         owner_xyz(a.dc, s, own);
 

@@ -30,6 +30,7 @@ struct DField {
     int32_t layout;  // 0 one array per component, 1 node-interleaved (collocated only)
     double r[3];     // n / L per axis
     int64_t sx;      // stored row length (n0 + 2 halo)
+    int64_t sy;      // stored rows of a plane (n1 + 2 halo)
     int64_t sxy;     // stored plane size
 };
 

@@ -252,8 +252,8 @@ typedef struct pm_ctx pm_ctx;
 /* Bytes of device workspace a context needs for particle pools of at most
  * pool_extent records (max over segments of base+cap), send buffers of at
  * most send_extent records, and nsub subdomains.  It holds, besides small
- * tables, one look-back word per tile, one slot per pool record for the
- * plain path, and a staging area of send_extent leaver records (137 bytes
+ * tables, the look-back state of every tile, four bytes per pool record for
+ * the plain path, and a staging area of send_extent leaver records (137 bytes
  * each: the 17 eight-byte values of a mid-step record of per-stage
  * migration, of which a per-step leaver uses 8, plus a direction byte).
  * 0 for invalid sizes (extents outside 0..2^34, nsub outside
@@ -335,7 +335,7 @@ pm_status pm_step(pm_ctx *ctx, const pm_field *field, const pm_decomp *decomp,
 /* pm_step for callers that cannot allocate: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  It needs no context
  * and no workspace: its scratch (the header words, tile and staging tables,
- * look-back words and the leavers' staging area that pm_step keeps in the
+ * look-back state and the leavers' staging area that pm_step keeps in the
  * workspace) is a fixed array of PM_NOALLOC_SCRATCH_BYTES in device memory
  * of the library, one per device, held until the process ends.  It calls no
  * allocating routine and queues only kernels, so a caller may capture it.

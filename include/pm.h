@@ -297,9 +297,8 @@ pm_status pm_interp_advance(pm_ctx *ctx, const pm_field *field,
 
 /* Steps 3-4 (mask, scan, pack) for segments [sub_first, sub_first+sub_count)
  * of `in` (left unchanged): writes every leaver to send segment s*27+d at
- * its scan slot, send->count for those segments, and the stayers before each
- * run of 64 records into the workspace for pm_compact_append.  Sect. 2.3.3
- * (stages 1-3). */
+ * its scan slot, send->count for those segments, and which records stay and
+ * where into the workspace for pm_compact_append.  Sect. 2.3.3 (stages 1-3). */
 pm_status pm_classify_scan_pack(pm_ctx *ctx, const pm_decomp *decomp,
                                 const pm_particles *in, pm_sendbufs *send,
                                 int32_t sub_first, int32_t sub_count,
@@ -309,8 +308,7 @@ pm_status pm_classify_scan_pack(pm_ctx *ctx, const pm_decomp *decomp,
  * the stayers of `in` compacted in order into `out`, then the particles
  * sent to each destination appended; writes out->count.  Needs
  * pm_classify_scan_pack to have run on these segments and on every
- * subdomain that neighbours them, on the same records and decomposition
- * (which tell the stayers apart), with no other classify call in between.
+ * subdomain that neighbours them, with no other classify call in between.
  * Sect. 3.2.2 (unpacking: compaction, then receive). */
 pm_status pm_compact_append(pm_ctx *ctx, const pm_decomp *decomp,
                             const pm_particles *in, const pm_sendbufs *send,

@@ -1344,9 +1344,40 @@ __global__ __launch_bounds__(WG) void k_advance(const KArgs a)
         flag_or(hdr, fl);
 }
 
-// Plain path, steps 3-4 (mask, scan): the stayers counted before each run of
-// 64 records of a segment to the workspace (ws.slot at the run's first record),
-// leavers to the staging area in scan order.
+// What k_classify leaves in ws.slot for a run of r <= 64 records of a segment,
+// m the lanes that stay: the stayers before the run and m's two halves in the
+// run's first three words, or, in a run too short for that, a word per record
+// with its slot (kNoSlot: leaves).  Words of a run's own records only.
+constexpr uint32_t kNoSlot = 0xffffffffu;
+
+__device__ __forceinline__ void put_run(uint32_t *run, int r, int lane, uint32_t before,
+                                        uint64_t m)
+{
+    if (lane >= 3 || lane >= r)
+        return;
+    uint32_t word = lane == 0 ? before : (uint32_t)(lane == 1 ? m : m >> 32);
+    if (r < 3)
+        word = (m >> lane & 1) ? before + (lane == 1 ? (uint32_t)(m & 1) : 0u) : kNoSlot;
+    run[lane] = word;
+}
+
+// The same words, one per lane (lane min(r, 3) - 1 and up: the last), read back.
+__device__ __forceinline__ uint64_t get_run(uint32_t word, int r, uint32_t &before)
+{
+    const uint32_t w0 = __builtin_amdgcn_readlane(word, 0);
+    const uint32_t w1 = __builtin_amdgcn_readlane(word, 1);
+    const uint32_t w2 = __builtin_amdgcn_readlane(word, 2);
+    before = w0;
+    if (r >= 3)
+        return (uint64_t)w2 << 32 | w1;
+    const bool s0 = r >= 1 && w0 != kNoSlot, s1 = r == 2 && w1 != kNoSlot;
+    before = s0 ? w0 : w1;
+    return (uint64_t)s0 | (uint64_t)s1 << 1;
+}
+
+// Plain path, steps 3-4 (mask, scan): which records of each run of 64 of a
+// segment stay, and the stayers before it, to the workspace (put_run), leavers
+// to the staging area in scan order.
 //
 // Bound by the reads of x (24 bytes a record).  As in k_step a tile's aggregate
 // is published at once and its look-back runs a tile later, so no workgroup
@@ -1382,10 +1413,10 @@ __global__ __launch_bounds__(WG) void k_classify(const KArgs a)
         owner_xyz(a.dc, s, own);
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
-            const int e = k * NW + w;
-            if (k * WG + w * 64 < nitems && lane == 0)
-                a.ws.slot[first + k * WG + w * 64] = P.base[0] + P.cnt[0][e];
+            const int e = k * NW + w, g = k * WG + w * 64;
             const int b = (int)(code[k] & 0xffu);
+            put_run(a.ws.slot + first + g, nitems - g, lane, P.base[0] + P.cnt[0][e],
+                    __ballot(b == PM_STAY));
             if (b >= 27 || b == PM_STAY)
                 continue;
             const int64_t m = (int64_t)P.base[1] + P.cnt[1][e] + (code[k] >> 8);
@@ -1620,10 +1651,10 @@ __global__ __launch_bounds__(256) void k_route(const KArgs a)
 
 // Plain path, unpacking part 1: stayers of `in` to their slots in `out`.  A
 // record's slot is the count that k_classify left for its run of 64 plus its
-// rank among the run's stayers, told apart by the same comparisons again
-// (cheaper than a slot written and read per record); each wave's runs are on
-// their own, whatever tiles they were counted in.  Bound by the records read
-// and written once, 16 streams at 4.3 TB/s: 1.58 ms on 52.7 million records.
+// rank among the run's stayers (less to write and read than a slot per record);
+// each wave's runs are on their own, whatever tiles they were counted in.
+// Bound by the records read and written once, 16 streams at 4.3 TB/s: 1.58 ms
+// on 52.7 million records.
 template <int WG, int ITEMS, typename FT>
 __global__ __launch_bounds__(WG) void k_compact(const KArgs a)
 {
@@ -1633,7 +1664,7 @@ __global__ __launch_bounds__(WG) void k_compact(const KArgs a)
         return;
     const int64_t total = hdr[kHdrTiles];
     const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
-    uint32_t fl = 0, seen = 0;  // seen: flags of the classification, raised by k_classify
+    uint32_t fl = 0;
     int cur = 0;
     for (int64_t q = blockIdx.x; q < total; q += gridDim.x, cur ^= 1) {
         if (tid == 0)
@@ -1643,18 +1674,17 @@ __global__ __launch_bounds__(WG) void k_compact(const KArgs a)
         const int64_t first = uniform(H[cur].first);
         const int nitems = uniform(H[cur].nitems);
         const int64_t obase = a.out.base[s], ocap = a.out.cap[s];
-        int own[3];
-        owner_xyz(a.dc, s, own);
         double X[ITEMS][3];
         FT V[ITEMS][3], tau[ITEMS];
         uint64_t id[ITEMS];
-        uint32_t before[ITEMS];
+        uint32_t word[ITEMS];
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
             const int g = k * WG + w * 64;
             const int i = g + lane;
             const int64_t p = first + (i < nitems ? i : nitems - 1);
-            before[k] = g < nitems ? a.ws.slot[first + g] : 0u;
+            const int last = (nitems - g < 3 ? nitems - g : 3) - 1;
+            word[k] = g < nitems ? a.ws.slot[first + g + (lane < last ? lane : last)] : 0u;
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 X[k][c] = __builtin_nontemporal_load(&a.in.x[c][p]);
@@ -1665,10 +1695,14 @@ __global__ __launch_bounds__(WG) void k_compact(const KArgs a)
         }
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
-            const bool stay = k * WG + tid < nitems && classify(a.dc, own, X[k], seen) == PM_STAY;
-            const uint64_t m = __ballot(stay);
+            const int r = nitems - (k * WG + w * 64);
+            if (r <= 0)
+                continue;
+            uint32_t before;
+            const uint64_t m = get_run(word[k], r, before);
+            const bool stay = m >> lane & 1;
             const int64_t slot =
-                (int64_t)before[k] + (int64_t)__popcll(m & ((1ull << lane) - 1ull));
+                (int64_t)before + (int64_t)__popcll(m & ((1ull << lane) - 1ull));
             if (stay && slot < ocap)
                 put_record<FT>(a.out, obase + slot, X[k], V[k], tau[k], id[k]);
             else if (stay)

@@ -76,8 +76,8 @@ struct DWS {
     uint16_t *status;      // [max_tiles] look-back: a tile's leavers + 1, 0 until known
     uint32_t *handed;      // [max_tiles / 64 + nsub + 1] leavers of a segment up to the end
                            // of each 64 of its tiles, + 1
-    uint32_t *slot;        // [pool_extent] stayers before each run of 64 records of a
-                           // segment, at the run's first record (plain path)
+    uint32_t *slot;        // [pool_extent] plain path: which records of each run of 64 of
+                           // a segment stay, and the stayers before it (put_run)
     // staging of the leavers, in scan order per segment: [stg_extent]
     double *stg_x[3];
     double *stg_v[3];      // read as float in the mixed mode

@@ -195,11 +195,13 @@ __device__ __forceinline__ void stencil_rows(const DField &f, const int c0[3], i
 }
 
 // Whether a stencil of any lane of the wave wraps around a periodic field
-// along x, so that its rows are not runs of two nodes.  Rare (one cell in n),
-// and decided for the whole wave on interleaved fields: with a branch per lane
-// around the wrapped nodes' loads every wave copied the 24 values once more and
-// waited for them there (2 x 10^7 records in 512 subdomains, float64: 1.31 ms
-// so, 1.15 without; split fields run no slower with it).
+// along x, so that its rows are not runs of two nodes.  Asked once per wave on
+// interleaved fields: with a branch per lane around the wrapped nodes' loads
+// every wave copies the 24 values once more and waits for them there (8 x 10^6
+// records of a 384^3 field in cell order, float64: 0.68 ms so, 0.57 without;
+// split fields run no slower with it).  In cell order few waves wrap; of waves
+// of 64 unrelated records 22% do at 256 cells an axis, 63% at 64, so they too
+// take whole rows, each lane with its own wrap (WRAP below).
 template <bool HALO>
 __device__ __forceinline__ bool any_wrap(bool wraps)
 {
@@ -208,31 +210,43 @@ __device__ __forceinline__ bool any_wrap(bool wraps)
 
 // The 24 node values of a stencil: v[c][2*r + x] for component c, row r and x
 // corner x.  Interleaved (ILV, the three components of a node next to each
-// other): each row's two nodes are one run of six values; the stencil must not
-// wrap along x (any_wrap).
-template <typename FT>
-__device__ __forceinline__ void stencil_load_ilv(const DField &f, const int64_t r[4], FT v[3][8])
+// other): each row's two nodes are one run of six values.  WRAP: a lane whose
+// stencil wraps along x loads the run that ends at its lower corner and the
+// nodes at 0 by themselves; else no lane's stencil may wrap.
+template <typename FT, bool WRAP>
+__device__ __forceinline__ void stencil_load_ilv(const DField &f, const int c0[3],
+                                                 const int64_t r[4], FT v[3][8])
 {
     const FT *u = (const FT *)f.u[0];
+    const bool wrap = WRAP && c0[0] + 1 == f.n[0];
+    const int back = wrap ? 1 : 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         FT w[6];
-        load_six<FT>(u + 3 * r[k], w);
+        load_six<FT>(u + 3 * (r[k] - back), w);
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
             v[c][2 * k] = w[c];
             v[c][2 * k + 1] = w[3 + c];
         }
     }
+    if (wrap) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                v[c][2 * k] = v[c][2 * k + 1];
+                v[c][2 * k + 1] = u[3 * (r[k] + 1 - f.n[0]) + c];
+            }
+    }
 }
 
-// The same where one stencil in float64 is all that a lane loads, wrap and all
-// (as in stencil_load_split).  A row's three loads stay together, so that its
-// line is asked for once, and the wrap is each lane's own, as a sparse wave's
-// points come from so many cells that too many waves would take any_wrap's
-// other path whole.  8.4 million points of 512^3: 0.66 ms so, 0.70 in the
+// The same where one stencil is all that a lane loads, wrap and all (as in
+// stencil_load_split).  A row's loads stay together, so that its line is asked
+// for once.  8.4 million points of 512^3 in float64: 0.66 ms so, 0.70 in the
 // compiler's order, 0.74 with any_wrap; 4.2 million of 254^3 with a halo:
-// 0.153, and 0.185 in the compiler's order.
+// 0.153, and 0.185 in the compiler's order.  Float32, 4 million points of 256^3
+// out of order: 0.363 ms so, 0.377 with any_wrap; in order the same.
 template <typename FT, bool HALO>
 __device__ __forceinline__ void stencil_load_rows(const DField &f, const int c0[3], FT v[3][8])
 {
@@ -304,13 +318,13 @@ __device__ __forceinline__ void stencil_load_split(const DField &f, const int c0
 // points of a split 256^3 field 0.186 ms against 0.206, the step with a halo
 // 0.330 against 0.335; the periodic step, which has a second stencil to wait
 // for anyway, 3.64 against 3.57 (2^26 records, 512^3).
-template <typename FT, bool HALO, bool ILV, bool APART = HALO>
+template <typename FT, bool HALO, bool ILV, bool WRAP, bool APART = HALO>
 __device__ __forceinline__ void stencil_load(const DField &f, const int c0[3], FT v[3][8])
 {
     int64_t r[4];
     stencil_rows<HALO>(f, c0, r);
     if constexpr (ILV)
-        stencil_load_ilv<FT>(f, r, v);
+        stencil_load_ilv<FT, WRAP>(f, c0, r, v);
     else
         stencil_load_split<FT, HALO, APART>(f, c0, r, v);
 }
@@ -380,28 +394,6 @@ __device__ __forceinline__ FT comp_eval(const FT v[8], const FT fr[3])
     return lerp(lerp(l00, l10, fr[1]), lerp(l01, l11, fr[1]), fr[2]);
 }
 
-// U at one stencil of a periodic interleaved field, every node loaded by
-// itself: for the waves with a stencil that wraps along x.
-template <typename FT>
-__device__ __forceinline__ void interp_wrapped(const DField &f, const int c0[3], const FT fr[3],
-                                               FT U[3])
-{
-    int64_t r[4];
-    stencil_rows<false>(f, c0, r);
-    const int64_t dx = c0[0] + 1 != f.n[0] ? 1 : 1 - (int64_t)f.n[0];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const FT *u = (const FT *)f.u[0] + c;
-        FT v[8];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            v[2 * k] = u[3 * r[k]];
-            v[2 * k + 1] = u[3 * (r[k] + dx)];
-        }
-        U[c] = comp_eval<FT>(v, fr);
-    }
-}
-
 // U(X) by trilinear interpolation (Sect. 2.2) from a field of arrangement FA.
 template <typename FT, bool HALO, int FA = kFieldSplit>
 __device__ __forceinline__ void interp(const DField &f, const double X[3], FT U[3],
@@ -422,16 +414,12 @@ __device__ __forceinline__ void interp(const DField &f, const double X[3], FT U[
     int c0[3];
     FT fr[3], v[3][8];
     stencil_index<FT, HALO>(f, X, c0, fr, fl);
-    if constexpr (FA == kFieldIlv && sizeof(FT) == 8) {
+    if constexpr (FA == kFieldIlv) {
         stencil_load_rows<FT, HALO>(f, c0, v);
         stencil_eval<FT>(v, fr, U);
         return;
     }
-    if (FA == kFieldIlv && any_wrap<HALO>(c0[0] == f.n[0] - 1)) {
-        interp_wrapped<FT>(f, c0, fr, U);
-        return;
-    }
-    stencil_load<FT, HALO, FA == kFieldIlv, true>(f, c0, v);
+    stencil_load<FT, HALO, false, false, true>(f, c0, v);
     stencil_eval<FT>(v, fr, U);
 }
 
@@ -466,9 +454,42 @@ __device__ __forceinline__ FT drag_factor(FT kappa, FT tau, const FT s[3])
     return (FT)1 + (FT)0.15 * exp2((FT)0.687 * log2(re));
 }
 
+// U at two stencils of a collocated field.  The second ones lie mostly on the
+// first ones' lines: issued once those have arrived they hit, issued along with
+// them they ask for every line again (2^26 records on a split 512^3 field: 3.7
+// ms so, 3.8 with both in flight; interleaved float64, 8 x 10^6 of 384^3 in cell
+// order: 0.61 and 0.63); the first stencil is evaluated while they come.
+// Interleaved float32 rows are few enough lines that it makes no difference in
+// cell order, and out of it the wait is only one more (never-sorted records of
+// which most change cells, 384^3: 1.07 ms without, 1.12 with), as it is for
+// wrapping waves, which mostly belong to such pools.  Where the two stencils
+// are one cell's, it is loaded once.
+template <typename FT, bool HALO, bool ILV, bool WRAP>
+__device__ __forceinline__ void two_stencils(const DField &f, const int c1[3], const FT fr1[3],
+                                             const int c2[3], const FT fr2[3], FT U1[3],
+                                             FT U2[3])
+{
+    const bool moved = c2[0] != c1[0] || c2[1] != c1[1] || c2[2] != c1[2];
+    FT S1[3][8], S2[3][8];
+    stencil_load<FT, HALO, ILV, WRAP>(f, c1, S1);
+    if constexpr (!ILV || (sizeof(FT) == 8 && !WRAP)) {
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    if (moved)
+        stencil_load<FT, HALO, ILV, WRAP>(f, c2, S2);
+    stencil_eval<FT>(S1, fr1, U1);
+    if (moved)
+        stencil_eval<FT>(S2, fr2, U2);
+    else
+        stencil_eval<FT>(S1, fr2, U2);
+}
+
 // Heun step of one particle.  The stage-2 position X* = X + dt V does not
 // depend on the stage-1 interpolation, so both stencils are located first;
-// most stage-2 stencils fall in the stage-1 cell and are not fetched again.  NL: the nonlinear drag factor, else f = 1.
+// most stage-2 stencils fall in the stage-1 cell and are not fetched again.
+// NL: the nonlinear drag factor, else f = 1.
 template <typename FT, bool HALO, bool NL, int FA>
 __device__ __forceinline__ void advance_one(const KArgs &a, double X[3], FT V[3], FT tau,
                                             uint32_t &fl)
@@ -506,29 +527,10 @@ __device__ __forceinline__ void advance_one(const KArgs &a, double X[3], FT V[3]
         FT fr1[3], fr2[3];
         stencil_index<FT, HALO>(a.f, X, c1, fr1, fl);
         stencil_index<FT, HALO>(a.f, Xs, c2, fr2, fl);
-        if (ILV && any_wrap<HALO>(c1[0] == last || c2[0] == last)) {
-            interp_wrapped<FT>(a.f, c1, fr1, U1);
-            interp_wrapped<FT>(a.f, c2, fr2, U2);
-        } else {
-            const bool moved = c2[0] != c1[0] || c2[1] != c1[1] || c2[2] != c1[2];
-            FT S1[3][8], S2[3][8];
-            stencil_load<FT, HALO, ILV>(a.f, c1, S1);
-            // the second stencils lie mostly on the first ones' lines: issued
-            // once those have arrived they hit, issued along with them they ask
-            // for every line again (2^26 records on a split 512^3 field: 3.7 ms
-            // so, 3.8 with both in flight); the first stencil is evaluated while
-            // they come
-            __builtin_amdgcn_sched_barrier(0);
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            if (moved)
-                stencil_load<FT, HALO, ILV>(a.f, c2, S2);
-            stencil_eval<FT>(S1, fr1, U1);
-            if (moved)
-                stencil_eval<FT>(S2, fr2, U2);
-            else
-                stencil_eval<FT>(S1, fr2, U2);
-        }
+        if (ILV && any_wrap<HALO>(c1[0] == last || c2[0] == last))
+            two_stencils<FT, HALO, ILV, true>(a.f, c1, fr1, c2, fr2, U1, U2);
+        else
+            two_stencils<FT, HALO, ILV, false>(a.f, c1, fr1, c2, fr2, U1, U2);
     }
     FT A1[3], Vs[3], s1[3], s2[3];
     const FT it = (FT)1 / tau;

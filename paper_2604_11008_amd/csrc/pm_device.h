@@ -1070,9 +1070,11 @@ __global__ __launch_bounds__(256) void k_prep(const KArgs a, int mode)
 // needs every group to have a running workgroup, which the in-order dispatch
 // of workgroups 0..xg-1 gives.
 //
-// `again`: the workgroup has had a tile.  Where there are at least as many
-// workgroups as tiles (those beyond the tiles left at once), each takes exactly
-// one ticket, and a second one would only keep its last tile waiting.
+// `again`: the workgroup has had a tile.  With one group and at least as many
+// workgroups as tiles each takes exactly one ticket, and a second one would only
+// keep its last tile waiting.  With several groups every workgroup draws until
+// its group is through: a group's lower tiles may be all that the others wait
+// for, and one that retired would make room for any group.
 template <int WG, int ITEMS>
 __device__ __forceinline__ bool next_tile(const KArgs &a, TileLds<WG, ITEMS> &L,
                                           int64_t total, const int64_t *ts, bool again)
@@ -1097,6 +1099,21 @@ __device__ __forceinline__ bool next_tile(const KArgs &a, TileLds<WG, ITEMS> &L,
     }
     __syncthreads();
     return L.h.q < total;
+}
+
+// Whether the workgroups before this one take every tile of its ticket group:
+// it may leave before it draws (65,536 records, 256 tiles for 512 workgroups: 29
+// us a step so, 31 with a ticket each).  Counted per group, since a group may own
+// many of few tiles (blocks of 256 give all of them to one group: 54 us, 63 with
+// a ticket each, 76 where the workgroups beyond the number of tiles left).
+__device__ __forceinline__ bool no_tile_left(const KArgs &a, uint32_t total)
+{
+    if (a.xg <= 1)
+        return blockIdx.x >= total;
+    const uint32_t xg = (uint32_t)a.xg, xb = (uint32_t)a.xb;  // at most 8 and 65536
+    const int32_t rest = (int32_t)(total % (xg * xb)) - (int32_t)(blockIdx.x % xg * xb);
+    const uint32_t own = total / (xg * xb) * xb + (uint32_t)min(max(rest, 0), a.xb);
+    return blockIdx.x / xg >= own;
 }
 
 // The tile table of the fused kernel's segment range, copied into LDS when it
@@ -1194,8 +1211,8 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(ITEMS >= 8 ?
     if (flags_now(hdr) & PM_F_LAYOUT)
         return;
     const int64_t total = hdr[kHdrTiles];
-    if (blockIdx.x >= total)
-        return;  // the workgroups before this one take every tile
+    if (no_tile_left(a, (uint32_t)total))
+        return;
     const int tid = threadIdx.x, w = tid >> 6;
     uint32_t fl = 0;
     int cur = 0;
@@ -1397,8 +1414,8 @@ __global__ __launch_bounds__(WG) void k_classify(const KArgs a)
     if (flags_now(hdr) & PM_F_LAYOUT)
         return;
     const int64_t total = hdr[kHdrTiles];
-    if (blockIdx.x >= total)
-        return;  // the workgroups before this one take every tile
+    if (no_tile_left(a, (uint32_t)total))
+        return;
     const int tid = threadIdx.x, lane = tid & 63, w = uniform(tid >> 6);
     uint32_t fl = 0;
     int cur = 0;
@@ -2069,8 +2086,8 @@ __global__ __launch_bounds__(WG) void k_stage(const KArgs a)
     if (flags_now(hdr) & PM_F_LAYOUT)
         return;
     const int64_t total = hdr[kHdrTiles];
-    if (blockIdx.x >= total)
-        return;  // the workgroups before this one take every tile
+    if (no_tile_left(a, (uint32_t)total))
+        return;
     const int tid = threadIdx.x, w = tid >> 6;
     uint32_t fl = 0;
     int cur = 0;

@@ -227,11 +227,13 @@ typedef struct {
  * pm_set_tuning selects the per-variant defaults (256 x 4; 256 x 2 for
  * mixed-precision periodic interleaved fields and for per-stage migration;
  * records per thread halved while the context's pool
- * extent gives fewer than two tiles per compute unit), which a context uses
- * until
+ * extent gives fewer than two tiles per compute unit; 512 x 4 for
+ * pm_classify_scan_pack and 256 x 2 for pm_compact_append, whatever the
+ * extent), which a context uses until
  * pm_set_tuning or pm_autotune fixes a shape; pm_get_tuning then reports the
  * shape of the last launch.  blocks_per_cu is the persistent grid's
- * workgroups per compute unit: 0 = the runtime's occupancy estimate; an
+ * workgroups per compute unit: 0 = the runtime's occupancy estimate (for
+ * pm_classify_scan_pack and pm_compact_append a figure of their own); an
  * explicit 1..32 may exceed it (surplus workgroups start as others retire;
  * tiles are claimed by ticket, so this cannot deadlock).  xcd_block is the
  * tile order of the persistent kernels: 0 = one ticket counter for all

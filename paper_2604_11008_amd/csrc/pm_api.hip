@@ -402,6 +402,37 @@ void set_groups(const pm_ctx *ctx, pm::KArgs &k, int grid)
     k.xb = grouped ? ctx->xcd_block : 1;
 }
 
+// Launch shape of the plain path's scan or compaction: the tuned one, else
+// `def`, which pm_get_tuning then reports.
+pm::Shape plain_shape(pm_ctx *ctx, pm::Shape def)
+{
+    const pm::Shape sh = ctx->shape_auto ? def : ctx->shape;
+    ctx->last_shape = sh;
+    return sh;
+}
+
+// Default workgroups per compute unit of the plain path's scan, 512 x 4
+// whatever the pool and its segments: tiles of 2048 records are few enough for
+// the look-back, and those of short segments cost few empty rows (scan, pack
+// and their set-up in float64, 256 x 1 / 256 x 4 / 256 x 16 / 512 x 4 at two a
+// compute unit: 3 x 10^5 records 36 / 27 / 30 / 25 us, 4 x 10^6 204 / 74 / 62 /
+// 54, 5.3 x 10^7 2400 / 669 / 417 / 419; 3 x 10^5 in 4096 segments 140 / 141 /
+// 168 / 143, 2 x 10^7 in 4096 segments 1125 / 585 / 497 / 449).  With one a
+// compute unit 5.3 x 10^7 take 662 us, with four 449.
+constexpr int kClassifyPerCu = 2;
+
+// The same for the compaction, 256 x 2.  Few workgroups of long runs suit the
+// memory best; where segments are many, tiles are shorter and each begins with
+// loads that depend on one another, which more workgroups hide (one, two, four
+// a compute unit: 4 x 10^6 records of one segment 115, 127, 129 us, of 512
+// segments 134, 128, 129, of 4096 segments 169, 152, 150; 5.3 x 10^7 of one
+// segment 1450, 1650, 1660, of 64 segments 1442, 1447, 1587; 3 x 10^5 in 4096
+// segments 76, 59, 51).
+int compact_per_cu(int32_t segments)
+{
+    return segments < 64 ? 1 : (segments < 1024 ? 2 : 4);
+}
+
 int append_cpt(int32_t count) { return std::max(1, 2048 / std::max(1, count)); }
 
 // Queue the fused step (prep, fused kernel, exchange) on `st`.
@@ -698,19 +729,16 @@ pm_status pm_classify_scan_pack(pm_ctx *ctx, const pm_decomp *decomp, const pm_p
     hipStream_t st = (hipStream_t)stream;
     k.sub_first = sub_first;
     k.sub_count = sub_count;
-    // tiles of the scan: 4096 records where the pool gives every compute unit
-    // two of them (the look-back passes over fewer tiles), else 1024 or 256
-    const int64_t pe = ctx->ws.pool_extent, cus = ctx->cus;
-    const int items = pe >= 4096 * 2 * cus ? 16 : (pe >= 1024 * 2 * cus ? 4 : 1);
-    (void)shape_for(ctx, mixed, false);  // the shape pm_get_tuning reports
-    k.tile = 256 * items;
-    k.xg = k.xb = 1;
+    const pm::Shape sh = plain_shape(ctx, {512, 4});
+    const int grid = ctx->cus * (ctx->blocks_per_cu > 0 ? ctx->blocks_per_cu : kClassifyPerCu);
+    k.tile = sh.wg * sh.items;
+    set_groups(ctx, k, grid);
     PM_HIP(pm::launch_prep(k,
                            pm::kPrepTiles | pm::kPrepStaging | pm::kPrepZeroLb |
                                pm::kPrepZeroCounts | pm::kPrepCheckIn | pm::kPrepCheckSend,
                            st),
            "prep launch");
-    PM_HIP(pm::launch_classify(k, mixed, items, ctx->cus, st), "classify launch");
+    PM_HIP(pm::launch_classify(k, sh, mixed, grid, st), "classify launch");
     PM_HIP(pm::launch_route(k, mixed, false, st), "route launch");
     return PM_OK;
 }
@@ -745,15 +773,16 @@ pm_status pm_compact_append(pm_ctx *ctx, const pm_decomp *decomp, const pm_parti
     hipStream_t st = (hipStream_t)stream;
     k.sub_first = sub_first;
     k.sub_count = sub_count;
-    const int items = ctx->ws.pool_extent >= 1024 * 2 * (int64_t)ctx->cus ? 4 : 1;
-    (void)shape_for(ctx, mixed, false);
-    k.tile = 256 * items;
+    const pm::Shape sh = plain_shape(ctx, {256, 2});
+    const int per = ctx->blocks_per_cu > 0 ? ctx->blocks_per_cu : compact_per_cu(sub_count);
+    const int cgrid = ctx->cus * per;
+    k.tile = sh.wg * sh.items;
     k.cpt = append_cpt(sub_count);
     PM_HIP(pm::launch_prep(k, pm::kPrepTiles | pm::kPrepCheckIn | pm::kPrepCheckOut |
                                   pm::kPrepCheckSend,
                            st),
            "prep launch");
-    PM_HIP(pm::launch_compact(k, mixed, items, ctx->cus, st), "compact launch");
+    PM_HIP(pm::launch_compact(k, sh, mixed, cgrid, st), "compact launch");
     const int grid = std::min(4096, sub_count * k.cpt);
     PM_HIP(pm::launch_append(k, mixed, std::max(1, grid), st), "append launch");
     return PM_OK;

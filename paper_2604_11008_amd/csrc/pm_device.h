@@ -1400,11 +1400,12 @@ __device__ __forceinline__ uint64_t get_run(uint32_t word, int r, uint32_t &befo
 //
 // Bound by the reads of x (24 bytes a record).  As in k_step a tile's aggregate
 // is published at once and its look-back runs a tile later, so no workgroup
-// waits for slower neighbours; the tile is large (up to 4096 records), since
-// the look-back passes over every tile in flight; a leaver (rare) is read
-// again when its slot is known.  52.7 million records of one segment: 376 us
-// (3.4 TB/s of x), against 1050 us with 1024-record tiles that waited for their
-// look-back and wrote every record's slot.
+// waits for slower neighbours; the default tile is large (2048 records), since
+// the look-back passes over every tile in flight; rows of a tile that no record
+// of a short segment reaches are skipped; a leaver (rare) is read again when its
+// slot is known.  52.7 million records of one segment: 387 us (3.3 TB/s of x),
+// against 1050 us with 1024-record tiles that waited for their look-back and
+// wrote every record's slot.
 template <int WG, int ITEMS, typename FT>
 __global__ __launch_bounds__(WG) void k_classify(const KArgs a)
 {
@@ -1470,17 +1471,22 @@ __global__ __launch_bounds__(WG) void k_classify(const KArgs a)
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
             const int i = k * WG + tid;
-            const int64_t p = first + (i < nitems ? i : nitems - 1);
+            if (k * WG + w * 64 < nitems) {  // a wave with any record
+                // records past the end of a ragged tile repeat its last one
+                const int64_t p = first + (i < nitems ? i : nitems - 1);
 #pragma unroll
-            for (int c = 0; c < 3; ++c)
-                X[k][c] = a.in.x[c][p];
+                for (int c = 0; c < 3; ++c)
+                    X[k][c] = a.in.x[c][p];
+            }
         }
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
-            // records past the end of a ragged tile repeat its last one
-            d[k] = classify(a.dc, own, X[k], fl);
-            if (k * WG + tid >= nitems)
-                d[k] = 0xff;
+            d[k] = 0xff;
+            if (k * WG + w * 64 < nitems) {
+                d[k] = classify(a.dc, own, X[k], fl);
+                if (k * WG + tid >= nitems)
+                    d[k] = 0xff;
+            }
         }
         tile_ranks<WG, ITEMS>(C, d, rank);
         publish_aggregate<WG, ITEMS>(a, C);
@@ -1672,8 +1678,8 @@ __global__ __launch_bounds__(256) void k_route(const KArgs a)
 // record's slot is the count that k_classify left for its run of 64 plus its
 // rank among the run's stayers (less to write and read than a slot per record);
 // each wave's runs are on their own, whatever tiles they were counted in.
-// Bound by the records read and written once, 16 streams at 4.3 TB/s: 1.58 ms
-// on 52.7 million records.
+// Bound by the records read and written once, 16 streams at 4.7 TB/s: 1.43 ms
+// on 52.7 million records (1.53 with four records a thread).
 template <int WG, int ITEMS, typename FT>
 __global__ __launch_bounds__(WG) void k_compact(const KArgs a)
 {

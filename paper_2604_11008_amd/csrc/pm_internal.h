@@ -155,8 +155,8 @@ hipError_t launch_sort(const KArgs &a, const DSort &s, int passes, bool mixed, i
                        int cus, hipStream_t st);
 hipError_t launch_step(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st);
 hipError_t launch_advance(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st);
-hipError_t launch_classify(const KArgs &a, bool mixed, int items, int cus, hipStream_t st);
-hipError_t launch_compact(const KArgs &a, bool mixed, int items, int cus, hipStream_t st);
+hipError_t launch_classify(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st);
+hipError_t launch_compact(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st);
 hipError_t launch_append(const KArgs &a, bool mixed, int grid, hipStream_t st);
 hipError_t launch_route(const KArgs &a, bool mixed, bool append, hipStream_t st,
                         bool ext = false);

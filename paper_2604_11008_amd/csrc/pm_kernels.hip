@@ -35,48 +35,28 @@ hipError_t launch_prep(const KArgs &a, int mode, hipStream_t st)
     return hipGetLastError();
 }
 
-// Tiles of the plain path's scan: the records a thread takes.
-#define PM_PLAIN_ITEMS(X) X(1) X(4) X(16)
-
-hipError_t launch_classify(const KArgs &a, bool mixed, int items, int cus, hipStream_t st)
-{
-    // two workgroups a compute unit: a tile of 4096 records holds 96 KB of
-    // loads in flight, and more workgroups queue for tickets at the start
-    // (10^6 records: 81 us for the exchange against 90 with four)
-    const int grid = cus * 2;
-#define PM_CLS_CASE(I)                                                                 \
-    if (items == I) {                                                                  \
-        if (mixed)                                                                     \
-            hipLaunchKernelGGL((k_classify<256, I, float>), dim3(grid), dim3(256), 0, st, a); \
-        else                                                                           \
-            hipLaunchKernelGGL((k_classify<256, I, double>), dim3(grid), dim3(256), 0, st, a); \
-        return hipGetLastError();                                                      \
+// The plain path's kernels in every launch shape.
+#define PM_PLAIN(K, W, I)                                                               \
+    if (sh.wg == W && sh.items == I) {                                                  \
+        if (mixed)                                                                      \
+            hipLaunchKernelGGL((K<W, I, float>), dim3(grid), dim3(W), 0, st, a);        \
+        else                                                                            \
+            hipLaunchKernelGGL((K<W, I, double>), dim3(grid), dim3(W), 0, st, a);       \
+        return hipGetLastError();                                                       \
     }
-    PM_PLAIN_ITEMS(PM_CLS_CASE)
-#undef PM_CLS_CASE
+#define PM_CLS_CASE(W, I) PM_PLAIN(k_classify, W, I)
+#define PM_CMP_CASE(W, I) PM_PLAIN(k_compact, W, I)
+
+hipError_t launch_classify(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st)
+{
+    PM_SHAPES(PM_CLS_CASE)
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_compact(const KArgs &a, bool mixed, int items, int cus, hipStream_t st)
+hipError_t launch_compact(const KArgs &a, Shape sh, bool mixed, int grid, hipStream_t st)
 {
-    // the larger the pool, the fewer workgroups: 16 streams of few long runs
-    // suit the memory better (exchange of 5.3e7 records 1.99 ms with one a
-    // compute unit, 2.11 with two, 2.12 with four; of 2e7 0.817, 0.809, 0.828;
-    // of 4e6 0.284, 0.257, 0.249)
-    const int64_t pe = a.ws.pool_extent;
-    const int grid = cus * (pe >= (1 << 25) ? 1 : (pe >= (1 << 23) ? 2 : 4));
-    if (items == 1) {
-        if (mixed)
-            hipLaunchKernelGGL((k_compact<256, 1, float>), dim3(grid), dim3(256), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_compact<256, 1, double>), dim3(grid), dim3(256), 0, st, a);
-    } else {
-        if (mixed)
-            hipLaunchKernelGGL((k_compact<256, 4, float>), dim3(grid), dim3(256), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_compact<256, 4, double>), dim3(grid), dim3(256), 0, st, a);
-    }
-    return hipGetLastError();
+    PM_SHAPES(PM_CMP_CASE)
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_append(const KArgs &a, bool mixed, int grid, hipStream_t st)

@@ -99,12 +99,13 @@ hipError_t interp_t(const KArgs &a, int grid, int64_t n, const double *x, const 
 {
     // Where points are fewer than cells, more workgroups on a compute unit push
     // each other's lines out of its L1: dynamic LDS that nothing uses leaves
-    // room for four (4.2 million points of 256^3: 0.187 ms with eight, 0.171
-    // with four).  At a point a cell and more the lines are shared and all eight
-    // hide more latency (4 million points in blobs of 100^3, mixed: 0.050 ms
-    // with four, 0.048 with eight; a uniform point a cell, 160^3: the same).
+    // room for four (8 million points of a split 256^3 field in float32: 0.193
+    // ms with eight, 0.180 with four).  Points in blobs share lines whatever
+    // their mean, but lose little by it (4 million: 0.110 and 0.113).  Not on
+    // interleaved fields, which ask for a third of the lines (8 million points:
+    // 0.126 with eight, 0.128 with four; 10 million in blobs: 0.146 and 0.161).
     const int64_t cells = (int64_t)a.f.n[0] * a.f.n[1] * a.f.n[2];
-    const size_t lds = n < cells ? 40 * 1024 : 0;
+    const size_t lds = FA != kFieldIlv && n < cells ? 40 * 1024 : 0;
     hipLaunchKernelGGL((k_interp<FT, H, FA>), dim3(grid), dim3(256), lds, st, a, n, x, y, z,
                        (FT *)ux, (FT *)uy, (FT *)uz);
     return hipGetLastError();
@@ -136,8 +137,9 @@ hipError_t launch_interp(const KArgs &a, bool mixed, int64_t n, const double *x,
                          const double *y, const double *z, void *ux, void *uy, void *uz,
                          hipStream_t st)
 {
-    const int64_t g = ((n + 255) / 256 + 7) / 8 * 8;
-    const int grid = (int)(g < 8 ? 8 : (g > 65536 ? 65536 : g));
+    const int64_t round = 8 * kInterpChunk;
+    const int64_t g = ((n + 255) / 256 + round - 1) / round * round;
+    const int grid = (int)(g > 65536 ? 65536 : g);
     return mixed ? interp_ft<float>(a, grid, n, x, y, z, ux, uy, uz, st)
                  : interp_ft<double>(a, grid, n, x, y, z, ux, uy, uz, st);
 }

@@ -69,9 +69,10 @@ struct WsLayout {
     int64_t max_tiles, stg_extent;
 };
 
-// Device workspace: header words, per-segment tables, one look-back word per
-// tile, the plain path's stayer slots (slot = false: none, for a workspace
-// that serves the fused step only), and the staging area of the leavers
+// Device workspace: header words, per-segment tables, eight bytes of look-back
+// state per tile, the plain path's stay masks and counts per run of 64 records,
+// in a word per record (slot = false: none, for a workspace that serves the
+// fused step only), and the staging area of the leavers
 // (one record per send-buffer slot, 8-byte fields, plus a direction byte).
 WsLayout ws_layout(int64_t pool_extent, int64_t send_extent, int32_t nsub, bool slot = true)
 {
@@ -112,9 +113,9 @@ void bind_ws(pm::DWS &ws, char *w, const WsLayout &L, int64_t pool_extent,
     ws.stay = (int64_t *)(w + L.stay);
     ws.migtot = (int64_t *)(w + L.migtot);
     ws.stg_start = (int64_t *)(w + L.stg_start);
-    // 8 bytes a tile: 2 of status (read in words of 4 tiles), and behind them
+    // 8 bytes a tile: 2 of status (in words of 4 tiles), and behind them
     // the 4 bytes per 64 tiles and per segment that are handed on
-    ws.status = (uint16_t *)(w + L.lb);
+    ws.status = (uint64_t *)(w + L.lb);
     ws.handed = (uint32_t *)(w + L.lb + (size_t)((L.max_tiles + 3) >> 2) * sizeof(uint64_t));
     ws.slot = slot ? (uint32_t *)(w + L.slot) : nullptr;
     const size_t fs = align256((size_t)L.stg_extent * 8);
@@ -929,7 +930,7 @@ pm_status pm_step(pm_ctx *ctx, const pm_field *field, const pm_decomp *decomp,
 // ---------------------------------------------------------------------------
 
 // The scratch of pm_step_noalloc (header words, tile and staging tables,
-// look-back words, the leavers' staging area): one copy per device, zero at
+// look-back state, the leavers' staging area): one copy per device, zero at
 // load, shared by every call on that device.  In host code this name is not
 // a device address; the address comes from hipGetSymbolAddress, per device.
 static __device__ __align__(256) unsigned char scratch[PM_NOALLOC_SCRATCH_BYTES];

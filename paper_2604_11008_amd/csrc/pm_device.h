@@ -18,9 +18,9 @@
 //     ticket, so a tile only ever waits on tiles that are already running;
 //   * within a tile, ranks come from two 64-lane ballots per stripe (stay,
 //     leave), a scan of the per-wave counts in LDS, and a look-back over the
-//     tiles of the same segment; a tile's status is one 16-bit word that holds
-//     its leavers, written and read with agent-scope atomics, so no fence is
-//     needed;
+//     tiles of the same segment; a tile's status is 16 bits that hold its
+//     leavers, four tiles to a word that is only accessed whole, with
+//     agent-scope atomics, so no fence is needed;
 //   * the fused kernel publishes a tile's aggregate at once and resolves its
 //     look-back and scatter one tile later, from an LDS stash;
 //   * leavers are rare: they go to a staging area and are split by direction
@@ -46,11 +46,6 @@ __device__ __forceinline__ uint64_t lb_load(const uint64_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-__device__ __forceinline__ void lb_store(uint64_t *p, uint64_t v)
-{
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 __device__ __forceinline__ void flag_or(uint32_t *hdr, uint32_t f)
 {
     __hip_atomic_fetch_or(hdr + kHdrFlags, f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -59,13 +54,6 @@ __device__ __forceinline__ void flag_or(uint32_t *hdr, uint32_t f)
 __device__ __forceinline__ uint32_t flags_now(const uint32_t *hdr)
 {
     return __hip_atomic_load(hdr + kHdrFlags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ uint64_t shfl64(uint64_t v, int src)
-{
-    const int lo = __shfl((int)(uint32_t)v, src, 64);
-    const int hi = __shfl((int)(uint32_t)(v >> 32), src, 64);
-    return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
 }
 
 template <typename T>
@@ -753,8 +741,9 @@ template <int WG, int ITEMS>
 __device__ __forceinline__ void publish_aggregate(const KArgs &a, const TileLds<WG, ITEMS> &L)
 {
     if (threadIdx.x == 0)
-        __hip_atomic_store(a.ws.status + L.h.q, (uint16_t)(L.agg[1] + 1), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_or(a.ws.status + (L.h.q >> 2),
+                              (uint64_t)(L.agg[1] + 1) << (16 * (int)(L.h.q & 3)),
+                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Whether one of the four 16-bit fields of x is 0.
@@ -781,7 +770,7 @@ __device__ __forceinline__ void walk_back(const KArgs &a, TileLds<WG, ITEMS> &L)
         return;
     // tile numbers fit 32 bits (pools of at most 2^34 records)
     const int q0 = uniform((int)L.h.qhead), q = uniform((int)L.h.q), j = q - q0;
-    const uint64_t *status = (const uint64_t *)a.ws.status;
+    const uint64_t *status = a.ws.status;
     uint32_t *handed = a.ws.handed + (q0 >> 6) + uniform(L.h.sl);
     uint32_t sum = 0, excl = 0;
     int end = q;  // the tiles from here on are in sum
@@ -1012,7 +1001,7 @@ __global__ __launch_bounds__(256) void k_prep(const KArgs a, int mode)
 
     if (mode & kPrepZeroLb) {
         for (int64_t i = gtid; i < (lb_words + 3) >> 2; i += gsize)
-            ((uint64_t *)a.ws.status)[i] = 0ull;
+            a.ws.status[i] = 0ull;
         for (int64_t i = gtid; i < (lb_words >> 6) + a.sub_count + 1; i += gsize)
             a.ws.handed[i] = 0u;
     }

@@ -73,7 +73,8 @@ struct DWS {
     int64_t *stay;         // [nsub] stayers per segment
     int64_t *migtot;       // [nsub] leavers per segment
     int64_t *stg_start;    // [PM_MAX_NSUB + 1] staging offset of each segment of the range
-    uint16_t *status;      // [max_tiles] look-back: a tile's leavers + 1, 0 until known
+    uint64_t *status;      // [max_tiles / 4, rounded up] look-back: 16 bits a tile, its
+                           // leavers + 1, 0 until known
     uint32_t *handed;      // [max_tiles / 64 + nsub + 1] leavers of a segment up to the end
                            // of each 64 of its tiles, + 1
     uint32_t *slot;        // [pool_extent] plain path: which records of each run of 64 of

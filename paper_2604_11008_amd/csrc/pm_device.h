@@ -33,6 +33,7 @@
 #include <type_traits>
 
 #include "pm_internal.h"
+#include "pm_lookback.h"
 
 namespace pm {
 namespace {
@@ -726,17 +727,18 @@ __device__ __forceinline__ void tile_ranks(TileLds<WG, ITEMS> &L, const int (&d)
 // before it later (the stayers before a tile are its records before it less
 // those: every tile but a segment's last is full).
 //
-// A tile's status is 16 bits (its leavers + 1, 0 until published), so that one
-// round trip of 4 words a lane covers 1024 tiles, more than are in flight; the
-// last tile of every 64 also hands on the leavers up to its end (+ 1), and a
-// walk ends at the nearest of those.  With two 31-bit counts a tile and 64 tiles
-// a round trip, the walk passed over the 512 to 768 tiles in flight in 8 to 12
-// round trips to memory, 10-25% of a step on segments of many tiles (measured
-// with the walk left out).  2^27 mixed-precision records on an interleaved
-// 1024^3 field: 6.55 -> 6.13 ms; 2^22 on 256^3: 0.189 -> 0.175 ms; 2^26 in
-// float64 on a split 512^3 field: 3.68 -> 3.58 ms.  (Sums over blocks of tiles
-// kept by atomic additions read less, but additions to one address go one
-// after the other, 10-20 ns each: 30-50% slower.)
+// A tile's status is 16 bits, so that one round trip of 4 words a lane covers
+// 1024 tiles, about what is in flight (two tiles a workgroup, 512 to 768
+// workgroups by default; a longer way takes another round); the last tile of
+// every 64 also hands on the leavers up to its end, and a walk ends at the
+// nearest of those (pm_lookback.h).  With two 31-bit counts a tile and 64 tiles
+// a round trip a walk took 8 to 12 round trips.  2^22 mixed-precision records on
+// an interleaved 256^3 field: 184 us a step so, 173 now; 2^22 in float64 with a
+// halo 328 and 322; the larger workloads change by less than their runs differ.
+// (Leaving the walk out altogether, and with it all waiting for earlier tiles,
+// had shown 10-25% on these; more of that is the waiting than the reads.  Sums
+// over blocks of tiles kept by atomic additions read less, but additions to one
+// address go one after the other, 10-20 ns each: 30-50% slower.)
 template <int WG, int ITEMS>
 __device__ __forceinline__ void publish_aggregate(const KArgs &a, const TileLds<WG, ITEMS> &L)
 {
@@ -744,12 +746,6 @@ __device__ __forceinline__ void publish_aggregate(const KArgs &a, const TileLds<
         __hip_atomic_fetch_or(a.ws.status + (L.h.q >> 2),
                               (uint64_t)(L.agg[1] + 1) << (16 * (int)(L.h.q & 3)),
                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Whether one of the four 16-bit fields of x is 0.
-__device__ __forceinline__ bool any_zero16(uint64_t x)
-{
-    return ((x - 0x1000100010001ull) & ~x & 0x8000800080008000ull) != 0;
 }
 
 __device__ __forceinline__ uint32_t wave_sum32(uint32_t v)
@@ -764,7 +760,7 @@ __device__ __forceinline__ uint32_t wave_sum32(uint32_t v)
 template <int WG, int ITEMS>
 __device__ __forceinline__ void walk_back(const KArgs &a, TileLds<WG, ITEMS> &L)
 {
-    constexpr int W = 4;  // status words (of 4 tiles) a lane reads at once
+    static_assert(WG * ITEMS < 0xffff, "a status holds the leavers of a tile");
     const int lane = threadIdx.x;
     if (lane >= 64)
         return;
@@ -776,40 +772,29 @@ __device__ __forceinline__ void walk_back(const KArgs &a, TileLds<WG, ITEMS> &L)
     int end = q;  // the tiles from here on are in sum
     bool more = j > 0;
     while (more) {
-        // lane: the end of the (lane + 1)-th block of 64 before `end`
-        const int b = ((end - q0) >> 6) - 1 - lane;
-        const int w0 = ((end + 3) >> 2) - 1 - lane;
+        const int b = walk_block(q0, end, lane);
         uint32_t h = b >= 0 ? __hip_atomic_load(handed + b, __ATOMIC_RELAXED,
                                                 __HIP_MEMORY_SCOPE_AGENT)
                             : (b == -1 ? 1u : 0u);
-        uint64_t v[W];
+        uint64_t v[kWalkWords];
 #pragma unroll
-        for (int i = 0; i < W; ++i) {
-            const int w = w0 - 64 * i;
-            v[i] = 4 * w + 4 > q0 ? lb_load(status + w) : 0;
+        for (int i = 0; i < kWalkWords; ++i) {
+            const int w = walk_word(end, lane, i);
+            v[i] = walk_reads(q0, w) ? lb_load(status + w) : 0;
         }
         const uint64_t found = __ballot(h != 0);
         const int k = found ? __ffsll((unsigned long long)found) - 1 : 63;
-        // the first tile whose leavers the walk has to add up itself
-        const int start = q0 + (((end - q0) >> 6) - k) * 64;
-        const int from = start > q0 ? start : q0;
-        const int low = 4 * ((end + 3) >> 2) - 256 * W;  // where the words read begin
+        const int from = walk_from(q0, end, k), low = walk_low(end);
 #pragma unroll
-        for (int i = 0; i < W; ++i) {
-            // the word's tiles in [from, end): fields f0 to f1 - 1
-            const int t = 4 * (w0 - 64 * i);
-            const int f0 = min(max(from - t, 0), 4);
-            const int f1 = min(max(end - t, 0), 4);
-            if (f0 < f1) {
-                const uint64_t in = (~0ull >> (64 - 16 * (f1 - f0))) << (16 * f0);
-                uint64_t word = v[i];
-                while (any_zero16(word | ~in)) {
+        for (int i = 0; i < kWalkWords; ++i) {
+            const int w = walk_word(end, lane, i);
+            const uint64_t mask = walk_mask(w, from, end);
+            if (mask) {
+                while (walk_missing(v[i], mask)) {
                     __builtin_amdgcn_s_sleep(1);
-                    word = lb_load(status + (w0 - 64 * i));
+                    v[i] = lb_load(status + w);
                 }
-                word &= in;
-                word = (word & 0xffff0000ffffull) + ((word >> 16) & 0xffff0000ffffull);
-                sum += (uint32_t)word + (uint32_t)(word >> 32) - (uint32_t)(f1 - f0);
+                sum += walk_sum(v[i], mask);
             }
         }
         if (low > from) {

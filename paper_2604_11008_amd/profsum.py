@@ -32,7 +32,7 @@ SOURCES = [os.path.join(PKG, "csrc", f) for f in ("pm_device.h", "pm_step_f64.hi
                                                     "pm_ilv_f32.hip", "pm_staged_f64.hip",
                                                     "pm_staged_f32.hip", "pm_staged_ilv_f64.hip",
                                                     "pm_staged_ilv_f32.hip", "pm_kernels.hip",
-                                                    "pm_internal.h")] + \
+                                                    "pm_internal.h", "pm_lookback.h")] + \
     [os.path.join(PKG, "gen.py")]
 COPY_KERNEL = "__amd_rocclr_copyBuffer"
 COPY_BYTES = 1 << 30

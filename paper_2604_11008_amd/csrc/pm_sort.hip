@@ -468,7 +468,7 @@ __global__ __launch_bounds__(kSortWG) void k_sort_gather(const KArgs a, DSort s,
 }
 
 // The workgroups of a launch over `work` jobs: one each up to eight a compute
-// unit (512 threads each, all the chip holds), the rest in strides.
+// unit (of 512 threads, twice what it holds at a time), the rest in strides.
 int sort_grid(int64_t work, int cus)
 {
     return (int)std::max<int64_t>(1, std::min<int64_t>(work, (int64_t)cus * 8));

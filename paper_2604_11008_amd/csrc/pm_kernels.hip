@@ -23,8 +23,8 @@ bool shape_supported(Shape sh)
 hipError_t launch_prep(const KArgs &a, int mode, hipStream_t st)
 {
     int64_t work = 1;
-    if (mode & kPrepZeroLb)  // a status word per four tiles
-        work = ((int64_t)a.ws.pool_extent / a.tile + a.sub_count + 5) / 4;
+    if (mode & kPrepZeroLb)  // four times the status words: workgroup 0 is busy with the tables
+        work = (int64_t)a.ws.pool_extent / a.tile + a.sub_count + 2;
     if (mode & (kPrepZeroCounts | kPrepCheckSend))
         work = work > (int64_t)a.dc.nsub * 27 ? work : (int64_t)a.dc.nsub * 27;
     if (mode & kPrepZeroCounts)

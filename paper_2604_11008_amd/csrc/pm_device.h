@@ -1789,25 +1789,21 @@ __global__ __launch_bounds__(256) void k_append(const KArgs a)
 // U at n points.  Bound by the field's lines between L2 and memory (a sparse
 // point's 12 row pairs are 12 lines, and a line is fetched again for each group
 // of points that reads it).  Workgroup b runs on XCD b mod 8; the points are
-// dealt to the XCDs in chunks of kInterpChunk workgroups, so that points next to
-// each other share an XCD's L2 and every XCD gets its share of the dense and of
-// the empty regions.  8.4 million points of a 512^3 field: 0.94 ms with
-// consecutive workgroups on different XCDs, 0.85 in chunks of 16, 0.85 in one
-// chunk an XCD; a million points of 256^3 in blobs: 69, 71 and 78 us; uniform in
-// float32: 66, 50 and 46.  The grid is a multiple of 8 kInterpChunk.
-constexpr int kInterpChunk = 16;
-
+// dealt to the XCDs in chunks of `chunk` workgroups (interp_chunk), so that points
+// next to each other share an XCD's L2 (8.4 million points of a split 512^3 field
+// in float64: 0.93 ms with consecutive workgroups on different XCDs, 0.84 in
+// eighths).  The grid is a multiple of 8.  Points fit memory, so their
+// workgroups fit 32 bits.
 template <typename FT, bool HALO, int FA>
 __global__ __launch_bounds__(256) void k_interp(const KArgs a, int64_t n, const double *x,
                                                 const double *y, const double *z, FT *ux,
-                                                FT *uy, FT *uz)
+                                                FT *uy, FT *uz, uint32_t chunk)
 {
-    constexpr int C = kInterpChunk;
     uint32_t fl = 0;
-    const int64_t blocks = (n + 255) / 256;
-    const int64_t turns = (blocks + 8 * C - 1) / (8 * C) * C;  // of workgroups 8 t to 8 t + 7
-    for (int64_t t = blockIdx.x >> 3; t < turns; t += gridDim.x >> 3) {
-        const int64_t b = (t / C * 8 + (blockIdx.x & 7)) * C + t % C;
+    const uint32_t blocks = (uint32_t)((n + 255) / 256);
+    const uint32_t turns = (blocks + 8 * chunk - 1) / (8 * chunk) * chunk;  // of 8 workgroups
+    for (uint32_t t = blockIdx.x >> 3; t < turns; t += gridDim.x >> 3) {
+        const int64_t b = (int64_t)(t / chunk * 8 + (blockIdx.x & 7)) * chunk + t % chunk;
         const int64_t i = b * 256 + threadIdx.x;
         if (i >= n)
             break;

@@ -93,8 +93,25 @@ hipError_t launch_route(const KArgs &a, bool mixed, bool append, hipStream_t st,
     return hipGetLastError();
 }
 
+// Workgroups of 256 points that an XCD takes in a row.  Points in blobs need
+// small chunks: an eighth of them a chunk leaves the XCDs with the dense regions
+// idle (10^6 points of 256^3 in blobs, split float64: 68 us with consecutive
+// workgroups on different XCDs, 71 in chunks of 16, 78 in eighths; 4 x 10^6
+// interleaved float32 82, 85, 95), and uniform points lose little by them (7 x
+// 10^6 of 400^3, float32: 347, 338, 349).  Eighths where so few points a cell
+// share lines that a chunk's neighbours matter, and so many points that every
+// eighth has its share of blobs (split float64 of 512^3, uniform: 5 x 10^6 744,
+// 741, 704; 8.4 x 10^6 933, 924, 838; 9 x 10^6 in blobs 628, 632, 640).
+// Interleaved fields show nothing for eighths.
+template <int FA>
+uint32_t interp_chunk(int64_t n, int64_t cells)
+{
+    const int64_t blocks = (n + 255) / 256;
+    return FA != kFieldIlv && n >= (1 << 22) && n < cells / 12 ? (uint32_t)((blocks + 7) / 8) : 16;
+}
+
 template <typename FT, bool H, int FA>
-hipError_t interp_t(const KArgs &a, int grid, int64_t n, const double *x, const double *y,
+hipError_t interp_t(const KArgs &a, int64_t n, const double *x, const double *y,
                     const double *z, void *ux, void *uy, void *uz, hipStream_t st)
 {
     // Where points are fewer than cells, more workgroups on a compute unit push
@@ -106,42 +123,43 @@ hipError_t interp_t(const KArgs &a, int grid, int64_t n, const double *x, const 
     // 0.126 with eight, 0.128 with four; 10 million in blobs: 0.146 and 0.161).
     const int64_t cells = (int64_t)a.f.n[0] * a.f.n[1] * a.f.n[2];
     const size_t lds = FA != kFieldIlv && n < cells ? 40 * 1024 : 0;
+    const uint32_t chunk = interp_chunk<FA>(n, cells);
+    const int64_t round = 8 * (int64_t)chunk;
+    const int64_t g = ((n + 255) / 256 + round - 1) / round * round;
+    const int grid = (int)(g > 65536 ? 65536 : g);
     hipLaunchKernelGGL((k_interp<FT, H, FA>), dim3(grid), dim3(256), lds, st, a, n, x, y, z,
-                       (FT *)ux, (FT *)uy, (FT *)uz);
+                       (FT *)ux, (FT *)uy, (FT *)uz, chunk);
     return hipGetLastError();
 }
 
 template <typename FT, bool H>
-hipError_t interp_h(const KArgs &a, int grid, int64_t n, const double *x, const double *y,
+hipError_t interp_h(const KArgs &a, int64_t n, const double *x, const double *y,
                     const double *z, void *ux, void *uy, void *uz, hipStream_t st)
 {
     switch (field_arr(a.f)) {
     case kFieldMac:
-        return interp_t<FT, H, kFieldMac>(a, grid, n, x, y, z, ux, uy, uz, st);
+        return interp_t<FT, H, kFieldMac>(a, n, x, y, z, ux, uy, uz, st);
     case kFieldIlv:
-        return interp_t<FT, H, kFieldIlv>(a, grid, n, x, y, z, ux, uy, uz, st);
+        return interp_t<FT, H, kFieldIlv>(a, n, x, y, z, ux, uy, uz, st);
     default:
-        return interp_t<FT, H, kFieldSplit>(a, grid, n, x, y, z, ux, uy, uz, st);
+        return interp_t<FT, H, kFieldSplit>(a, n, x, y, z, ux, uy, uz, st);
     }
 }
 
 template <typename FT>
-hipError_t interp_ft(const KArgs &a, int grid, int64_t n, const double *x, const double *y,
+hipError_t interp_ft(const KArgs &a, int64_t n, const double *x, const double *y,
                      const double *z, void *ux, void *uy, void *uz, hipStream_t st)
 {
-    return a.f.halo != 0 ? interp_h<FT, true>(a, grid, n, x, y, z, ux, uy, uz, st)
-                         : interp_h<FT, false>(a, grid, n, x, y, z, ux, uy, uz, st);
+    return a.f.halo != 0 ? interp_h<FT, true>(a, n, x, y, z, ux, uy, uz, st)
+                         : interp_h<FT, false>(a, n, x, y, z, ux, uy, uz, st);
 }
 
 hipError_t launch_interp(const KArgs &a, bool mixed, int64_t n, const double *x,
                          const double *y, const double *z, void *ux, void *uy, void *uz,
                          hipStream_t st)
 {
-    const int64_t round = 8 * kInterpChunk;
-    const int64_t g = ((n + 255) / 256 + round - 1) / round * round;
-    const int grid = (int)(g > 65536 ? 65536 : g);
-    return mixed ? interp_ft<float>(a, grid, n, x, y, z, ux, uy, uz, st)
-                 : interp_ft<double>(a, grid, n, x, y, z, ux, uy, uz, st);
+    return mixed ? interp_ft<float>(a, n, x, y, z, ux, uy, uz, st)
+                 : interp_ft<double>(a, n, x, y, z, ux, uy, uz, st);
 }
 
 hipError_t launch_touch(const KArgs &a, bool mixed, uint64_t *bits, hipStream_t st)

@@ -34,3 +34,26 @@ def test_chunks(n, cells):
         U = ctx.interp(f, torch.from_numpy(X).cuda()).cpu().numpy()
         assert ctx.get_status() == 0
         assert np.abs(U - ref).max() <= (64 + 64 * cells) * eps * umax
+
+
+def test_sparse_points_in_eighths():
+    """Few points a cell and many of them: an eighth of the workgroups to an XCD.
+    The same points in another order, and some by themselves, give the same bits."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    n, cells = (1 << 22) + 3 * 256 + 11, 384
+    print(f"[test] {n} points, {cells}^3 cells", flush=True)
+    g = torch.Generator("cuda").manual_seed(3)
+    u = [torch.randn(cells ** 3, generator=g, device="cuda", dtype=torch.float32)
+         for _ in range(3)]
+    X = torch.rand(3, n, generator=g, device="cuda", dtype=torch.float64) * L
+    ctx = pm.Context(1, 1, 1)
+    for stag in (False, True):
+        f = pm.DeviceField(u, cells, 0, L, stagger=stag)
+        U = ctx.interp(f, X)
+        assert torch.equal(U, ctx.interp(f, X.flip(1).contiguous()).flip(1))
+        k = torch.arange(0, n, 4099, device="cuda")
+        assert torch.equal(U[:, k], ctx.interp(f, X[:, k].contiguous()))
+        assert torch.equal(U[:, -300:], ctx.interp(f, X[:, -300:].contiguous()))
+        assert bool((U != 0).all())
+    assert ctx.get_status() == 0

@@ -450,8 +450,15 @@ pm_status queue_step(pm_ctx *ctx, pm::KArgs &k, bool mixed, hipStream_t st, bool
            "prep launch");
     if (timed)
         PM_HIP(hipEventRecord(ctx->events[2 * ctx->tcount], st), "event record");
-    const int grid =
+    int grid =
         persistent_grid(ctx, sh, mixed, k.f.halo != 0, k.drag != 0, pm::field_arr(k.f));
+    // Fewer than two tiles for each workgroup: at most two a compute unit.  Three
+    // (the float32 kernels) would hold every tile at once, each with its loads in
+    // flight and then waiting for all the others (4 x 10^5 mixed records of 64^3,
+    // 256 x 2, three and two a compute unit: split 46.9 and 45.5 us a step in cell
+    // order, 68.6 and 59.8 never sorted; staggered 49.9 and 46.9, 72.6 and 64.9).
+    if (ctx->blocks_per_cu == 0 && ctx->ws.pool_extent / k.tile < 2 * (int64_t)grid)
+        grid = std::min(grid, 2 * ctx->cus);
     set_groups(ctx, k, grid);
     PM_HIP(pm::launch_step(k, sh, mixed, grid, st), "fused step launch");
     if (timed) {

@@ -1300,7 +1300,9 @@ __global__ __launch_bounds__(WG) __attribute__((amdgpu_waves_per_eu(ITEMS >= 8 ?
         flag_or(hdr, fl);
 }
 
-// Plain path, steps 1-2: in-place advance of the range's records.
+// Plain path, steps 1-2: in-place advance of the range's records.  Bound as the
+// fused step's gathers are (4 x 10^6 records of 256^3 in cell order, float64: 292
+// us split, 248 interleaved, 296 staggered; mixed 217, 158, 225).
 template <int WG, int ITEMS, typename FT, bool HALO, bool NL, int FA>
 __global__ __launch_bounds__(WG) void k_advance(const KArgs a)
 {

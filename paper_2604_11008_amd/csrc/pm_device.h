@@ -169,6 +169,19 @@ __device__ __forceinline__ void load_six(const FT *p, FT w[6])
         w[i] = q.w[i];
 }
 
+// Three of them: one node.
+template <typename FT>
+__device__ __forceinline__ void load_three(const FT *p, FT w[3])
+{
+    struct Three {
+        FT w[3];
+    } q;
+    __builtin_memcpy(&q, p, sizeof q);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        w[i] = q.w[i];
+}
+
 // Stored index of the lower x corner of a stencil's four rows (y and z corner:
 // 00, 10, 01, 11).
 template <bool HALO>
@@ -190,7 +203,7 @@ __device__ __forceinline__ void stencil_rows(const DField &f, const int c0[3], i
 // records of a 384^3 field in cell order, float64: 0.68 ms so, 0.57 without;
 // split fields run no slower with it).  In cell order few waves wrap; of waves
 // of 64 unrelated records 22% do at 256 cells an axis, 63% at 64, so they too
-// take whole rows, each lane with its own wrap (WRAP below).
+// must not cost much more (WRAP below).
 template <bool HALO>
 __device__ __forceinline__ bool any_wrap(bool wraps)
 {
@@ -199,15 +212,32 @@ __device__ __forceinline__ bool any_wrap(bool wraps)
 
 // The 24 node values of a stencil: v[c][2*r + x] for component c, row r and x
 // corner x.  Interleaved (ILV, the three components of a node next to each
-// other): each row's two nodes are one run of six values.  WRAP: a lane whose
-// stencil wraps along x loads the run that ends at its lower corner and the
-// nodes at 0 by themselves; else no lane's stencil may wrap.
+// other): each row's two nodes are one run of six values.  WRAP: lanes of the
+// wave wrap along x.  In float64 every lane then loads its nodes one by one, four
+// loads a row instead of three, which takes no more registers than whole rows;
+// in float32 a lane that wraps loads the run that ends at its lower corner and
+// the nodes at 0 by themselves (4 x 10^6 records never sorted, most changing
+// cells, 128^3: 298 us a step so, 316 node by node).
 template <typename FT, bool WRAP>
 __device__ __forceinline__ void stencil_load_ilv(const DField &f, const int c0[3],
                                                  const int64_t r[4], FT v[3][8])
 {
     const FT *u = (const FT *)f.u[0];
     const bool wrap = WRAP && c0[0] + 1 == f.n[0];
+    if constexpr (WRAP && sizeof(FT) == 8) {
+        const int64_t dx = wrap ? 1 - (int64_t)f.n[0] : 1;
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                FT w[3];
+                load_three<FT>(u + 3 * (r[k] + (x ? dx : 0)), w);
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    v[c][2 * k + x] = w[c];
+            }
+        return;
+    }
     const int back = wrap ? 1 : 0;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -452,13 +482,24 @@ __device__ __forceinline__ FT drag_factor(FT kappa, FT tau, const FT s[3])
 // cell order, and out of it the wait is only one more (never-sorted records of
 // which most change cells, 384^3: 1.07 ms without, 1.12 with), as it is for
 // wrapping waves, which mostly belong to such pools.  Where the two stencils
-// are one cell's, it is loaded once.
-template <typename FT, bool HALO, bool ILV, bool WRAP>
+// are one cell's, it is loaded once.  LEAN: one stencil's registers (wrapping
+// waves of the float64 kernel with nonlinear drag, which has none left: with both
+// it spills in every wave, 2^25 records on 512^3 2.3 ms a step instead of 2.0).
+template <typename FT, bool HALO, bool ILV, bool WRAP, bool LEAN>
 __device__ __forceinline__ void two_stencils(const DField &f, const int c1[3], const FT fr1[3],
                                              const int c2[3], const FT fr2[3], FT U1[3],
                                              FT U2[3])
 {
     const bool moved = c2[0] != c1[0] || c2[1] != c1[1] || c2[2] != c1[2];
+    if constexpr (LEAN) {
+        FT S[3][8];
+        stencil_load<FT, HALO, ILV, WRAP>(f, c1, S);
+        stencil_eval<FT>(S, fr1, U1);
+        if (moved)
+            stencil_load<FT, HALO, ILV, WRAP>(f, c2, S);
+        stencil_eval<FT>(S, fr2, U2);
+        return;
+    }
     FT S1[3][8], S2[3][8];
     stencil_load<FT, HALO, ILV, WRAP>(f, c1, S1);
     if constexpr (!ILV || (sizeof(FT) == 8 && !WRAP)) {
@@ -512,14 +553,15 @@ __device__ __forceinline__ void advance_one(const KArgs &a, double X[3], FT V[3]
         }
     } else {
         constexpr bool ILV = FA == kFieldIlv;
+        constexpr bool LEAN = NL && sizeof(FT) == 8;
         int c1[3], c2[3];
         FT fr1[3], fr2[3];
         stencil_index<FT, HALO>(a.f, X, c1, fr1, fl);
         stencil_index<FT, HALO>(a.f, Xs, c2, fr2, fl);
         if (ILV && any_wrap<HALO>(c1[0] == last || c2[0] == last))
-            two_stencils<FT, HALO, ILV, true>(a.f, c1, fr1, c2, fr2, U1, U2);
+            two_stencils<FT, HALO, ILV, true, LEAN>(a.f, c1, fr1, c2, fr2, U1, U2);
         else
-            two_stencils<FT, HALO, ILV, false>(a.f, c1, fr1, c2, fr2, U1, U2);
+            two_stencils<FT, HALO, ILV, false, false>(a.f, c1, fr1, c2, fr2, U1, U2);
     }
     FT A1[3], Vs[3], s1[3], s2[3];
     const FT it = (FT)1 / tau;

@@ -213,18 +213,18 @@ __device__ __forceinline__ bool any_wrap(bool wraps)
 // The 24 node values of a stencil: v[c][2*r + x] for component c, row r and x
 // corner x.  Interleaved (ILV, the three components of a node next to each
 // other): each row's two nodes are one run of six values.  WRAP: lanes of the
-// wave wrap along x.  In float64 every lane then loads its nodes one by one, four
-// loads a row instead of three, which takes no more registers than whole rows;
-// in float32 a lane that wraps loads the run that ends at its lower corner and
-// the nodes at 0 by themselves (4 x 10^6 records never sorted, most changing
-// cells, 128^3: 298 us a step so, 316 node by node).
-template <typename FT, bool WRAP>
+// wave wrap along x, and load the run that ends at their lower corner and the
+// nodes at 0 by themselves; or, NODES, every lane loads its nodes one by one,
+// which takes no more registers than the rows of other waves but is slower where
+// there is room (4 x 10^6 records never sorted, most changing cells, 128^3:
+// float64 450 us a step by rows and 464 by nodes, float32 298 and 316).
+template <typename FT, bool WRAP, bool NODES>
 __device__ __forceinline__ void stencil_load_ilv(const DField &f, const int c0[3],
                                                  const int64_t r[4], FT v[3][8])
 {
     const FT *u = (const FT *)f.u[0];
     const bool wrap = WRAP && c0[0] + 1 == f.n[0];
-    if constexpr (WRAP && sizeof(FT) == 8) {
+    if constexpr (WRAP && NODES) {
         const int64_t dx = wrap ? 1 - (int64_t)f.n[0] : 1;
 #pragma unroll
         for (int k = 0; k < 4; ++k)
@@ -337,13 +337,13 @@ __device__ __forceinline__ void stencil_load_split(const DField &f, const int c0
 // points of a split 256^3 field 0.186 ms against 0.206, the step with a halo
 // 0.330 against 0.335; the periodic step, which has a second stencil to wait
 // for anyway, 3.64 against 3.57 (2^26 records, 512^3).
-template <typename FT, bool HALO, bool ILV, bool WRAP, bool APART = HALO>
+template <typename FT, bool HALO, bool ILV, bool WRAP, bool APART = HALO, bool NODES = false>
 __device__ __forceinline__ void stencil_load(const DField &f, const int c0[3], FT v[3][8])
 {
     int64_t r[4];
     stencil_rows<HALO>(f, c0, r);
     if constexpr (ILV)
-        stencil_load_ilv<FT, WRAP>(f, c0, r, v);
+        stencil_load_ilv<FT, WRAP, NODES>(f, c0, r, v);
     else
         stencil_load_split<FT, HALO, APART>(f, c0, r, v);
 }
@@ -482,9 +482,10 @@ __device__ __forceinline__ FT drag_factor(FT kappa, FT tau, const FT s[3])
 // cell order, and out of it the wait is only one more (never-sorted records of
 // which most change cells, 384^3: 1.07 ms without, 1.12 with), as it is for
 // wrapping waves, which mostly belong to such pools.  Where the two stencils
-// are one cell's, it is loaded once.  LEAN: one stencil's registers (wrapping
-// waves of the float64 kernel with nonlinear drag, which has none left: with both
-// it spills in every wave, 2^25 records on 512^3 2.3 ms a step instead of 2.0).
+// are one cell's, it is loaded once.  LEAN: one stencil at a time, node by node,
+// for the wrapping waves of the float64 kernel with nonlinear drag, which has no
+// registers left: with both, by rows, every wave spills (2^25 records on 512^3 2.3
+// ms a step instead of 2.0).
 template <typename FT, bool HALO, bool ILV, bool WRAP, bool LEAN>
 __device__ __forceinline__ void two_stencils(const DField &f, const int c1[3], const FT fr1[3],
                                              const int c2[3], const FT fr2[3], FT U1[3],
@@ -493,10 +494,10 @@ __device__ __forceinline__ void two_stencils(const DField &f, const int c1[3], c
     const bool moved = c2[0] != c1[0] || c2[1] != c1[1] || c2[2] != c1[2];
     if constexpr (LEAN) {
         FT S[3][8];
-        stencil_load<FT, HALO, ILV, WRAP>(f, c1, S);
+        stencil_load<FT, HALO, ILV, WRAP, HALO, LEAN>(f, c1, S);
         stencil_eval<FT>(S, fr1, U1);
         if (moved)
-            stencil_load<FT, HALO, ILV, WRAP>(f, c2, S);
+            stencil_load<FT, HALO, ILV, WRAP, HALO, LEAN>(f, c2, S);
         stencil_eval<FT>(S, fr2, U2);
         return;
     }
